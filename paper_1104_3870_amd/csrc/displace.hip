@@ -177,21 +177,27 @@ extern "C" int laph_displace(laph_ctx_t c, const double *U, int dir, int sign, i
     LAPH_API_END(c)
 }
 
+void overlap_slices(laph_ctx *c, const double2 *a, int na, const double2 *b, int nb, int k0, int k1, int k2,
+                    double2 *phase, double2 *out)
+{
+    const long V3 = c->g.V3;
+    hipLaunchKernelGGL(k_phase, dim3(nblocks_for(V3, 256)), dim3(256), 0, c->stream, phase, c->g.ns, k0, k1, k2);
+    const unsigned gn = (na + zg::kTM - 1) / zg::kTM, gm = (nb + zg::kTN - 1) / zg::kTN;
+    LAPH_CHECK(gm <= 65535 && c->g.nt <= 65535, LAPH_EINVAL, "too many fields for one launch");
+    LAPH_CHECK(3 * V3 < (1L << 31), LAPH_EINVAL, "slice too large");
+    OverlapS os{a, b, phase, out, na, nb, (int)(3 * V3)};
+    hipLaunchKernelGGL((zg::k_zgemm<16, OverlapS>), dim3(gn, gm, c->g.nt), dim3(256), 0, c->stream, os);
+    LAPH_HIP(hipGetLastError());
+}
+
 extern "C" int laph_mom_overlap(laph_ctx_t c, const double *a, int na, const double *b, int nb, const int *k,
                                 double *out)
 {
     LAPH_API_BEGIN(c)
     g_current_ctx = c;
     LAPH_CHECK(a && b && k && out && na > 0 && nb > 0, LAPH_EINVAL, "bad arguments");
-    const long V3 = c->g.V3;
-    double2 *ph = (double2 *)ctx_named(c, "ovl.phase", sizeof(double2) * V3);
-    hipLaunchKernelGGL(k_phase, dim3(nblocks_for(V3, 256)), dim3(256), 0, c->stream, ph, c->g.ns, k[0], k[1], k[2]);
-    const unsigned gn = (na + zg::kTM - 1) / zg::kTM, gm = (nb + zg::kTN - 1) / zg::kTN;
-    LAPH_CHECK(gm <= 65535 && c->g.nt <= 65535, LAPH_EINVAL, "too many fields for one launch");
-    LAPH_CHECK(3 * V3 < (1L << 31), LAPH_EINVAL, "slice too large");
-    OverlapS os{(const double2 *)a, (const double2 *)b, (const double2 *)ph, (double2 *)out, na, nb, (int)(3 * V3)};
-    hipLaunchKernelGGL((zg::k_zgemm<16, OverlapS>), dim3(gn, gm, c->g.nt), dim3(256), 0, c->stream, os);
-    LAPH_HIP(hipGetLastError());
+    double2 *ph = (double2 *)ctx_named(c, "ovl.phase", sizeof(double2) * c->g.V3);
+    overlap_slices(c, (const double2 *)a, na, (const double2 *)b, nb, k[0], k[1], k[2], ph, (double2 *)out);
     LAPH_API_END(c)
 }
 

@@ -6,19 +6,22 @@
 
 namespace {
 
-// one lane per (slice t, spatial site); vectors of slice t start at base + t * stride
-__global__ __launch_bounds__(256) void k_lap(const double2 *__restrict__ us, const double2 *__restrict__ in,
+constexpr int kLapLanes = 256;
+
+// one lane per (slice t, spatial site), a workgroup's sites in one slice; vectors of slice t
+// start at base + t * stride.  DOT: block sums of <dot, out> and |out|^2 (see lap_fused)
+template <bool DOT>
+__global__ __launch_bounds__(kLapLanes) void k_lap(const double2 *__restrict__ us, const double2 *__restrict__ in,
                                              long in_stride, const double2 *__restrict__ prev, long prev_stride,
                                              double2 *__restrict__ out, long out_stride, int ns, int nt, long V,
-                                             double alpha, double beta, double gamma, const int *__restrict__ skip)
+                                             double alpha, double beta, double gamma, int nblk,
+                                             const double2 *__restrict__ dot, long dot_stride, double *__restrict__ sums)
 {
-    unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    long s = (long)b * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    long V3 = V / nt;
-    int t = (int)(s / V3);
-    if (skip && skip[t]) return;
-    long r = s - (long)t * V3;
+    const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+    const int t = (int)(b / nblk);
+    const long V3 = V / nt, r = (long)(b - (unsigned)t * nblk) * kLapLanes + threadIdx.x, s = (long)t * V3 + r;
+    double dre = 0.0, dim = 0.0, nrm = 0.0;
+    if (r < V3) {
     int x = (int)(r % ns);
     long q = r / ns;
     int y = (int)(q % ns);
@@ -67,40 +70,73 @@ __global__ __launch_bounds__(256) void k_lap(const double2 *__restrict__ us, con
         double2 o = cadd(cscale(acc[a], alpha), cscale(self[a], beta));
         if (prev) o = cadd(o, cscale(prev[t * prev_stride + r * 3 + a], gamma));
         vo[r * 3 + a] = o;
+        if (DOT) {
+            const double2 q = dot[t * dot_stride + r * 3 + a];
+            dre += q.x * o.x + q.y * o.y;
+            dim += q.x * o.y - q.y * o.x;
+            nrm += cnorm2(o);
+        }
+    }
+    }
+    if (DOT) {
+        __shared__ double red[3][kLapLanes / 64];
+        for (int w = 32; w > 0; w >>= 1) {
+            dre += __shfl_down(dre, w, 64);
+            dim += __shfl_down(dim, w, 64);
+            nrm += __shfl_down(nrm, w, 64);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            red[0][threadIdx.x >> 6] = dre;
+            red[1][threadIdx.x >> 6] = dim;
+            red[2][threadIdx.x >> 6] = nrm;
+        }
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            double v = 0.0;
+            for (int w = 0; w < kLapLanes / 64; w++) v += red[threadIdx.x][w];
+            sums[(long)b * 3 + threadIdx.x] = v;
+        }
     }
 }
 
 }  // namespace
 
+int lap_blocks(const Geom &g) { return (int)((g.V3 + kLapLanes - 1) / kLapLanes); }
+
 void lap_fused(laph_ctx *c, const double2 *us, const double2 *in, long in_stride, const double2 *prev,
                long prev_stride, double2 *out, long out_stride, double alpha, double beta, double gamma,
-               const int *skip)
+               const double2 *dot, long dot_stride, double *sums)
 {
-    long V = c->g.V;
-    hipLaunchKernelGGL(k_lap, dim3(nblocks_for(V, 256)), dim3(256), 0, c->stream, us, in, in_stride, prev,
-                       prev_stride, out, out_stride, c->g.ns, c->g.nt, V, alpha, beta, gamma, skip);
+    const int nblk = lap_blocks(c->g);
+    const dim3 grid((unsigned)(nblk * (long)c->g.nt));
+    if (sums)
+        hipLaunchKernelGGL(k_lap<true>, grid, dim3(kLapLanes), 0, c->stream, us, in, in_stride, prev, prev_stride, out,
+                           out_stride, c->g.ns, c->g.nt, c->g.V, alpha, beta, gamma, nblk, dot, dot_stride, sums);
+    else
+        hipLaunchKernelGGL(k_lap<false>, grid, dim3(kLapLanes), 0, c->stream, us, in, in_stride, prev, prev_stride, out,
+                           out_stride, c->g.ns, c->g.nt, c->g.V, alpha, beta, gamma, nblk, dot, dot_stride, sums);
     LAPH_HIP(hipGetLastError());
 }
 
 // out = T_order(B) in, B = 1 + cc (Lap + lamC); w0, w1 scratch of the same shape
 void cheb_apply(laph_ctx *c, const double2 *us, const double2 *in, long in_stride, double2 *out, long out_stride,
-                double2 *w0, double2 *w1, long w_stride, double lamL, double lamC, int order, const int *skip)
+                double2 *w0, double2 *w1, long w_stride, double lamL, double lamC, int order, double *sums)
 {
     double cc = 2.0 / (lamL - lamC);
     double b0 = 1.0 + cc * lamC;  // B = cc * Lap + b0
     if (order == 0) {
-        lap_fused(c, us, in, in_stride, nullptr, 0, out, out_stride, 0.0, 1.0, 0.0, skip);
+        lap_fused(c, us, in, in_stride, nullptr, 0, out, out_stride, 0.0, 1.0, 0.0, in, in_stride, sums);
         return;
     }
     if (order == 1) {
-        lap_fused(c, us, in, in_stride, nullptr, 0, out, out_stride, cc, b0, 0.0, skip);
+        lap_fused(c, us, in, in_stride, nullptr, 0, out, out_stride, cc, b0, 0.0, in, in_stride, sums);
         return;
     }
     // T_1 -> w0; then T_k = 2 B T_{k-1} - T_{k-2}, rotating buffers so T_order lands in out
     const double2 *tm2 = in;
     long s2 = in_stride;
     double2 *bufs[2] = {w0, w1};
-    lap_fused(c, us, in, in_stride, nullptr, 0, w0, w_stride, cc, b0, 0.0, skip);
+    lap_fused(c, us, in, in_stride, nullptr, 0, w0, w_stride, cc, b0, 0.0);
     const double2 *tm1 = w0;
     long s1 = w_stride;
     int nb = 1;
@@ -115,7 +151,8 @@ void cheb_apply(laph_ctx *c, const double2 *us, const double2 *in, long in_strid
             sd = w_stride;
             nb ^= 1;
         }
-        lap_fused(c, us, tm1, s1, tm2, s2, dst, sd, 2.0 * cc, 2.0 * b0, -1.0, skip);
+        lap_fused(c, us, tm1, s1, tm2, s2, dst, sd, 2.0 * cc, 2.0 * b0, -1.0, in, in_stride,
+                  k == order ? sums : nullptr);
         tm2 = tm1;
         s2 = s1;
         tm1 = dst;
@@ -138,7 +175,7 @@ extern "C" int laph_laplacian_apply(laph_ctx_t c, const double *U, const double 
     double2 *us = prepare_soa(c, U);
     long V3 = c->g.V3;
     // one launch covers all slices: a "slice stride" of V3*3 makes the layout contiguous
-    lap_fused(c, us, (const double2 *)v, V3 * 3, nullptr, 0, (double2 *)out, V3 * 3, 1.0, 0.0, 0.0, nullptr);
+    lap_fused(c, us, (const double2 *)v, V3 * 3, nullptr, 0, (double2 *)out, V3 * 3, 1.0, 0.0, 0.0);
     LAPH_API_END(c)
 }
 
