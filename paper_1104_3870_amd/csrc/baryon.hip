@@ -4,7 +4,7 @@
 // With the trivial displacement every LapH-smeared quark sink is varphi = V_s f, so
 //   B(t) = sum_{abg} c_abg sum_{n1 n2 n3} T[t][n1][n2][n3] f1[t][a][n1] f2[t][b][n2] f3[t][g][n3]
 // with the eigenvector tensor T[t][n1][n2][n3] = sum_x e^{-ip.x} eps_abc V_n1(x,a) V_n2(x,b)
-// V_n3(x,c) (totally antisymmetric: computed for n1 < n2, the rest by symmetry).  The
+// V_n3(x,c) (totally antisymmetric: computed for n1 < n2 < n3, the rest by symmetry).  The
 // contraction over (n1, n2, n3) for all dilution triples is three batched complex products:
 //   X[n1 n2][k g]   = sum_n3 T[n1 n2][n3] F3[n3][k g]
 //   Y[n1][j b][k g] = sum_n2 F2[n2][j b] X[n1 n2][k g]
@@ -107,190 +107,194 @@ void zgemm(laph_ctx *c, const Zgemm &g, long batch)
 }
 
 // ------------------------------------------------------- eigenvector tensor
-// T[t][n1][n2][n3] = sum_{x,c} (e^{-ip.x} V_n1(x) x V_n2(x))_c V_n3(x, c), (u x w)_c =
-// eps_abc u_a w_b, is totally antisymmetric, so only n1 < n2 < n3 is computed and each
-// value is written to its six images (the tensor is zeroed first, which leaves every entry
-// with a repeated index at zero).  One block per (n1, slice, chunk of tile pairs): for the
-// 16-row tiles a <= b of n2 and n3 that can hold n1 < n2 < n3, the products
-// A[n2][(x c)] B[(x c)][n3] with A the cross products (formed while staging) and
-// B = V_n3, on the FP64 matrix cores; the rows of A and B from the block's first tile on
-// are staged through LDS four sites at a time, and the block's four waves take the pairs
-// in turn.  Loading each stage one stage ahead (registers) and staging only the rows the
-// block's pairs read took the 24^3 x 128, N_v = 112 tensor from 527 to 470 ms.
-constexpr int kBT = 16;  // MFMA tile
-constexpr int kBK = 12;  // K per stage: four sites x three colours
-constexpr int kBP = 6;   // tile pairs per wave and block
+// X(a, b, c) = sum_x e^{-ip.x} (V_a(x) x V_b(x)) . V_c(x) for a < b < c as one product per
+// slice: rows are the pairs (a, b), formed as cross products in the lanes that feed the
+// matrix cores, columns the vectors c > b, K = 3 Ns^3.  Matrix and vector instructions share
+// the FP64 pipe on gfx950 (measured: they add up), so the vector work per product is what
+// this split keeps down: each row serves at least about N_v / 2 columns because the pairs
+// are taken from the low side (b < N_v / 2, columns above b) and, by the mirror i -> N_v - 1
+// - i, from the high side; 90% of the issued products are wanted at N_v = 112 (66% with one
+// workgroup per first index).
+//
+// A workgroup's four waves take 16 pairs each and the same T <= kPT tiles of 16 columns.  K
+// advances four sites a stage.  Lane l holds pair l % 16 at site l / 16: the three colours
+// of its cross product are the A operands of three matrix steps (k = l / 16), so no A value
+// passes through LDS.  Column vectors are staged in LDS (double-buffered, rows of 13 double2:
+// conflict-free 16-byte reads), the next stage's loads in flight during the products.
+//
+// 24^3 x 128, N_v = 112: 190 ms (9.7e12 useful flops at 51 TFLOP/s, 58 TFLOP/s issued, of
+// the 73 that back-to-back matrix instructions reach), 450 ms with one workgroup per first
+// index, both operands staged through LDS.  At most 7 tiles: 4 and 5 (more workgroups per
+// slice, each row formed more often) took 6% and 3% longer.
+constexpr int kPT = 7;       // column tiles of 16 per workgroup
+constexpr int kPS = 4;       // sites per stage
+constexpr int kPR = 3 * kPS + 1;  // LDS row stride (double2)
+// LDS rows of a stage: whole elements for all 256 lanes (rows past a tile count's own hold
+// vectors nobody reads; a condition would sink the loads below the products)
+constexpr int kPRows = ((kPT * 16 * 3 * kPS + 255) / 256 * 256 + 3 * kPS - 1) / (3 * kPS);
+constexpr int kPBuf = kPRows * kPR;
 
-__host__ __device__ inline int tri_pairs(int u) { return u * (u + 1) / 2; }
-
-// SA, SB: staging elements of A (rows x 4 sites) and B (rows x kBK) per lane whose global
-// loads are held in registers one stage ahead, so that the loads of stage k + 1 are in
-// flight during the matrix products of stage k (SA = 0: staged directly, for row counts
-// whose elements would not fit the registers).  The phase-multiplied V_n1 of a stage's
-// four sites is formed once per stage into LDS.
-template <int SA, int SB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_baryon_tensor_tri(
-    const double2 *__restrict__ V, const double2 *__restrict__ ph, int nv, long V3, int T, double2 *__restrict__ out)
+// row r of the pairs a < b ordered by b
+__host__ __device__ inline void pair_of(long r, int &a, int &b)
 {
-    extern __shared__ double lds[];
-    const int NP = T * kBT + 4;  // LDS row stride (doubles)
-    double *ar = lds, *ai = ar + kBK * NP, *br = ai + kBK * NP, *bi = br + kBK * NP;
-    __shared__ double2 su[2][kBK];  // e^{-ip.x} V_n1(x) of the stage's sites, double-buffered
-    const int n1 = blockIdx.x, t = blockIdx.z;
-    const int amin = (n1 + 1) / kBT;  // first n2 tile holding an n2 > n1
-    if (amin >= T) return;
-    const int np = tri_pairs(T - amin);
-    const int p0 = blockIdx.y * 4 * kBP;
-    if (p0 >= np) return;  // uniform over the block
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-    // this wave's pairs p = p0 + wave + 4 j, decoded to (a, b), a <= b
-    int pa[kBP], pb[kBP];
+    int q = (int)((1.0 + sqrt(1.0 + 8.0 * (double)r)) * 0.5);
+    while ((long)q * (q - 1) / 2 > r) q--;
+    while ((long)(q + 1) * q / 2 <= r) q++;
+    b = q;
+    a = (int)(r - (long)q * (q - 1) / 2);
+}
+
+struct PairArgs {
+    const double2 *V, *ph;
+    double2 *out;
+    int nv, nt, low;    // low: vectors on the low side, N_v / 2
+    int blocks, chunks;  // workgroups per slice and side (pairs), column chunks
+    int xcd;             // slices dealt to the XCDs in turn (nt a multiple of 8)
+    long V3;
+};
+
+template <int T>
+__device__ __forceinline__ void pair_tile(const PairArgs &P, double2 *lds, int t, int side, long row0, long rows,
+                                          int ctop)
+{
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, lr = l & 15, ls = l >> 4, nv = P.nv;
+    const long K = 3 * P.V3;
+    const double2 *Vt = P.V + (long)t * nv * K;
+    auto vec = [&](int i) { return side ? nv - 1 - i : i; };
+    // this lane's pair (past the end: the last one, not stored) and its site of a stage
+    int a, b;
+    pair_of(min(row0 + 16 * wave + lr, rows - 1), a, b);
+    const double2 *pa = Vt + (long)vec(a) * K + 3 * ls, *pb = Vt + (long)vec(b) * K + 3 * ls, *pp = P.ph + ls;
+    // this lane's staging elements: column row e / 12, element e % 12 of its 12 per stage
+    constexpr int NB = (T * 16 * 3 * kPS + 255) / 256;
+    const double2 *pc[NB];
+    int dst[NB];
 #pragma unroll
-    for (int j = 0; j < kBP; j++) {
-        int p = p0 + wave + 4 * j, a = amin;
-        pa[j] = -1;
-        pb[j] = -1;
-        if (p < np && p < p0 + 4 * kBP) {
-            while (p >= T - a) {
-                p -= T - a;
-                a++;
-            }
-            pa[j] = a;
-            pb[j] = a + p;
-        }
+    for (int q = 0; q < NB; q++) {
+        const int e = threadIdx.x + 256 * q, r = e / (3 * kPS), k = e - r * (3 * kPS);
+        // column r of tile j is c = ctop - 16 (j + 1) + r % 16 (below 0: unused, any vector)
+        const int c = ctop - 16 * (r / 16 + 1) + (r & 15);
+        dst[q] = r * kPR + k;
+        pc[q] = Vt + (long)vec(max(c, 0)) * K + k;
     }
-    zg::d4 cr[kBP], ci[kBP];
+    zg::d4 cr[T], ci[T];
 #pragma unroll
-    for (int j = 0; j < kBP; j++) {
+    for (int j = 0; j < T; j++) {
         cr[j] = zg::d4{0.0, 0.0, 0.0, 0.0};
         ci[j] = zg::d4{0.0, 0.0, 0.0, 0.0};
     }
-    const long K = 3 * V3;
-    const double2 *Vt = V + (long)t * nv * K;
-    // rows from the first tile any pair of this block reads
-    const int rlo = kBT * amin, rows = T * kBT;
-    const double2 z2 = make_double2(0.0, 0.0);
-    // lanes 0..11: e^{-ip.x} V_n1(x)_c of the stage's (site, colour) k into su[buf][k]
-    auto u_stage = [&](long k0, int buf) {
-        if (threadIdx.x < kBK) {
-            const long kk = k0 + threadIdx.x, x = kk / 3;
-            su[buf][threadIdx.x] = kk < K ? cmul(ph[x], Vt[(long)n1 * K + kk]) : z2;
+    double2 va[3], vb[3], vp, vc[NB];
+    auto fetch = [&](long k) {  // the loads of stage k
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            va[c] = pa[3 * kPS * k + c];
+            vb[c] = pb[3 * kPS * k + c];
+        }
+        vp = pp[kPS * k];
+#pragma unroll
+        for (int q = 0; q < NB; q++) vc[q] = pc[q][3 * kPS * k];
+    };
+    double xr[3], xi[3];
+    auto put = [&](double2 *buf) {
+#pragma unroll
+        for (int q = 0; q < NB; q++) buf[dst[q]] = vc[q];
+#pragma unroll
+        for (int c = 0; c < 3; c++) va[c] = cmul(vp, va[c]);
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;
+            xr[c] = va[c1].x * vb[c2].x - va[c1].y * vb[c2].y - va[c2].x * vb[c1].x + va[c2].y * vb[c1].y;
+            xi[c] = va[c1].x * vb[c2].y + va[c1].y * vb[c2].x - va[c2].x * vb[c1].y - va[c2].y * vb[c1].x;
         }
     };
-    // A element e = (m, site xs): the cross product of su with V_m(x)
-    auto a_in = [&](int e, long k0, double2 (&w)[3]) {
-        const int m = rlo + (e >> 2);
-        const long x = k0 / 3 + (e & 3);
-        if (m < rows && x < V3 && m < nv) {
-            const double2 *wp = Vt + ((long)m * V3 + x) * 3;
-            w[0] = wp[0];
-            w[1] = wp[1];
-            w[2] = wp[2];
-        } else {
-            w[0] = w[1] = w[2] = z2;
-        }
-    };
-    auto a_out = [&](int e, const double2 (&w)[3], int buf) {
-        const int m = rlo + (e >> 2), xs = e & 3;
-        if (m >= rows) return;
-        const double2 u0 = su[buf][3 * xs], u1 = su[buf][3 * xs + 1], u2 = su[buf][3 * xs + 2];
-        const double2 c3[3] = {csub(cmul(u1, w[2]), cmul(u2, w[1])), csub(cmul(u2, w[0]), cmul(u0, w[2])),
-                               csub(cmul(u0, w[1]), cmul(u1, w[0]))};
-#pragma unroll
-        for (int cc = 0; cc < 3; cc++) {
-            ar[(3 * xs + cc) * NP + m] = c3[cc].x;
-            ai[(3 * xs + cc) * NP + m] = c3[cc].y;
-        }
-    };
-    // B element e = (n3, k): V_n3 at K index k0 + k (K contiguous per vector)
-    auto b_in = [&](int e, long k0) {
-        const int q = e / kBK, n = rlo + q;
-        const long kk = k0 + (e - q * kBK);
-        // an explicit branch: a select against the local zero would load through a flat
-        // address
-        double2 v = z2;
-        if (n < rows && kk < K && n < nv) v = Vt[(long)n * K + kk];
-        return v;
-    };
-    auto b_out = [&](int e, double2 v) {
-        const int q = e / kBK, n = rlo + q, k = e - q * kBK;
-        if (n >= rows) return;
-        br[k * NP + n] = v.x;
-        bi[k * NP + n] = v.y;
-    };
-    const int na = (rows - rlo) * 4, nb = (rows - rlo) * kBK;
-    double2 ra[SA > 0 ? SA : 1][3], rb[SB > 0 ? SB : 1];
-    if constexpr (SA > 0) {
-#pragma unroll
-        for (int q = 0; q < SA; q++) a_in(threadIdx.x + 256 * q, 0, ra[q]);
-#pragma unroll
-        for (int q = 0; q < SB; q++) rb[q] = b_in(threadIdx.x + 256 * q, 0);
-    }
-    u_stage(0, 0);
+    fetch(0);
+    put(lds);
     __syncthreads();
-    int buf = 0;
-    for (long k0 = 0; k0 < K; k0 += kBK) {
-        if constexpr (SA > 0) {
+    const long stages = P.V3 / kPS;
+    const double2 *base = lds + lr * kPR + 3 * ls;
+    for (long k = 0; k < stages; k++) {
+        const double2 *buf = base + (k & 1) * kPBuf;
+        // (the last stage has nothing ahead of it and fetches its own again)
+        fetch(min(k + 1, stages - 1));
 #pragma unroll
-            for (int q = 0; q < SA; q++)
-                if (threadIdx.x + 256 * q < na) a_out(threadIdx.x + 256 * q, ra[q], buf);
+        for (int c = 0; c < 3; c++) {
+            double2 y[T];
 #pragma unroll
-            for (int q = 0; q < SB; q++)
-                if (threadIdx.x + 256 * q < nb) b_out(threadIdx.x + 256 * q, rb[q]);
-        } else {
-            for (int e = threadIdx.x; e < na; e += blockDim.x) {
-                a_in(e, k0, ra[0]);
-                a_out(e, ra[0], buf);
+            for (int j = 0; j < T; j++) y[j] = buf[j * 16 * kPR + c];
+            const double ni = -xi[c];
+#pragma unroll
+            for (int j = 0; j < T; j++) {
+                cr[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[c], y[j].x, cr[j], 0, 0, 0);
+                ci[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[c], y[j].y, ci[j], 0, 0, 0);
             }
-            for (int e = threadIdx.x; e < nb; e += blockDim.x) b_out(e, b_in(e, k0));
+#pragma unroll
+            for (int j = 0; j < T; j++) {
+                cr[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ni, y[j].y, cr[j], 0, 0, 0);
+                ci[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[c], y[j].x, ci[j], 0, 0, 0);
+            }
         }
-        // the next stage's V_n1 goes to the other buffer, read after the next barrier
-        if (k0 + kBK < K) u_stage(k0 + kBK, buf ^ 1);
+        put(lds + ((k + 1) & 1) * kPBuf);
         __syncthreads();
-        if constexpr (SA > 0) {
-            // the next stage's loads, consumed after this stage's products
-            if (k0 + kBK < K) {
-#pragma unroll
-                for (int q = 0; q < SA; q++) a_in(threadIdx.x + 256 * q, k0 + kBK, ra[q]);
-#pragma unroll
-                for (int q = 0; q < SB; q++) rb[q] = b_in(threadIdx.x + 256 * q, k0 + kBK);
-            }
-        }
-        // one K step of 4 at a time: its LDS operands of the six pairs (48 registers) are
-        // what the compiler keeps in flight, leaving room for the next stage's loads
-#pragma unroll 1
-        for (int kk = 0; kk < kBK; kk += 4) {
-#pragma unroll
-            for (int j = 0; j < kBP; j++) {
-                if (pa[j] < 0) continue;  // uniform over the wave
-                const int ia = (kk + lk) * NP + kBT * pa[j] + lr, ib = (kk + lk) * NP + kBT * pb[j] + lr;
-                const double xr = ar[ia], xi = ai[ia], yr = br[ib], yi = bi[ib];
-                cr[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr, yr, cr[j], 0, 0, 0);
-                cr[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xi, yi, cr[j], 0, 0, 0);
-                ci[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr, yi, ci[j], 0, 0, 0);
-                ci[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xi, yr, ci[j], 0, 0, 0);
-            }
-        }
-        __syncthreads();
-        buf ^= 1;
     }
-    // element v of lane l: C[lk + 4 v][lr] of the pair's tile (see zgemm_mfma.h)
-    const long nv2 = (long)nv * nv, base = (long)t * nv * nv2;
+    // element v of lane l: pair l / 16 + 4 v, column l % 16 of the tile
+    const long nv2 = (long)nv * nv;
+    double2 *out = P.out + (long)t * nv * nv2;
 #pragma unroll
-    for (int j = 0; j < kBP; j++) {
-        if (pa[j] < 0) continue;
+    for (int v = 0; v < 4; v++) {
+        const long r = row0 + 16 * wave + ls + 4 * v;
+        if (r >= rows) continue;
+        int ia, ib;
+        pair_of(r, ia, ib);
+        const long na = vec(ia), nb = vec(ib);
 #pragma unroll
-        for (int v = 0; v < 4; v++) {
-            const int n2 = kBT * pa[j] + lk + 4 * v, n3 = kBT * pb[j] + lr;
-            if (n2 <= n1 || n3 <= n2 || n3 >= nv) continue;
+        for (int j = 0; j < T; j++) {
+            const int ic = ctop - 16 * (j + 1) + lr;
+            if (ic <= ib) continue;
+            const long nc = vec(ic);
             const double2 q = make_double2(cr[j][v], ci[j][v]), mq = make_double2(-cr[j][v], -ci[j][v]);
-            out[base + n1 * nv2 + (long)n2 * nv + n3] = q;
-            out[base + n1 * nv2 + (long)n3 * nv + n2] = mq;
-            out[base + n2 * nv2 + (long)n1 * nv + n3] = mq;
-            out[base + n2 * nv2 + (long)n3 * nv + n1] = q;
-            out[base + n3 * nv2 + (long)n1 * nv + n2] = q;
-            out[base + n3 * nv2 + (long)n2 * nv + n1] = mq;
+            out[na * nv2 + nb * nv + nc] = q;
+            out[nb * nv2 + nc * nv + na] = q;
+            out[nc * nv2 + na * nv + nb] = q;
+            out[na * nv2 + nc * nv + nb] = mq;
+            out[nb * nv2 + na * nv + nc] = mq;
+            out[nc * nv2 + nb * nv + na] = mq;
         }
+    }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_baryon_tensor_pairs(const PairArgs P)
+{
+    __shared__ double2 lds[2 * kPBuf];
+    const int per = 2 * P.blocks * P.chunks;
+    long g = blockIdx.x;
+    int t;
+    if (P.xcd) {  // workgroup g runs on XCD g % 8: a slice's workgroups share that XCD's L2
+        const long q = g >> 3;
+        t = (int)(q / per) * 8 + (int)(g & 7);
+        g = q % per;
+    } else {
+        t = (int)(g / per);
+        g -= (long)t * per;
+    }
+    const int chunk = (int)(g / (2 * P.blocks)), side = (int)(g & 1);
+    const int h = side ? P.nv - P.low : P.low;
+    const long row0 = 64 * ((g % (2 * P.blocks)) >> 1), rows = (long)h * (h - 1) / 2;
+    if (row0 >= rows) return;
+    // columns c > b of the workgroup's lowest b, in tiles of 16 from the top
+    int a, b;
+    pair_of(row0, a, b);
+    const int need = (P.nv - 1 - b + 15) / 16, parts = (need + kPT - 1) / kPT, tc = (need + parts - 1) / parts;
+    const int first = chunk * tc, T = min(tc, need - first);
+    if (T <= 0) return;
+    const int ctop = P.nv - 16 * first;
+    switch (T) {
+    case 1: pair_tile<1>(P, lds, t, side, row0, rows, ctop); break;
+    case 2: pair_tile<2>(P, lds, t, side, row0, rows, ctop); break;
+    case 3: pair_tile<3>(P, lds, t, side, row0, rows, ctop); break;
+    case 4: pair_tile<4>(P, lds, t, side, row0, rows, ctop); break;
+    case 5: pair_tile<5>(P, lds, t, side, row0, rows, ctop); break;
+    case 6: pair_tile<6>(P, lds, t, side, row0, rows, ctop); break;
+    default: pair_tile<7>(P, lds, t, side, row0, rows, ctop); break;
     }
 }
 
@@ -413,25 +417,19 @@ extern "C" int laph_baryon_tensor(laph_ctx_t c, const double *evecs, int nv, con
     const long V3 = c->g.V3;
     double2 *ph = (double2 *)ctx_named(c, "bar.phase", sizeof(double2) * V3);
     hipLaunchKernelGGL(k_phase3, dim3(nblocks_for(V3, 256)), dim3(256), 0, c->stream, ph, c->g.ns, k[0], k[1], k[2]);
-    const int tiles = (nv + kBT - 1) / kBT;
-    const size_t lds = sizeof(double) * 4 * kBK * (size_t)(tiles * kBT + 4);
-    LAPH_CHECK(lds <= 160 * 1024, LAPH_EINVAL, "nv too large: the tensor kernel stages all N_v vectors in LDS");
+    LAPH_CHECK(nv <= 416, LAPH_EINVAL, "nv too large");
     LAPH_CHECK(c->g.nt <= 65535 && 3 * V3 < (1L << 31), LAPH_EINVAL, "lattice too large for one launch");
-    // up to 128 rows (N_v <= 128) each lane holds two A and six B elements of the next stage
-    const bool pre = tiles * kBT <= 128;
-    const void *kern = pre ? (const void *)k_baryon_tensor_tri<2, 6> : (const void *)k_baryon_tensor_tri<0, 0>;
-    if (lds > 64 * 1024)
-        LAPH_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const long total = (long)c->g.nt * nv * nv * nv;
     hipLaunchKernelGGL(k_zero2, dim3(nblocks_for(total, 256)), dim3(256), 0, c->stream, (double2 *)T, total);
-    const int chunks = (tri_pairs(tiles) + 4 * kBP - 1) / (4 * kBP);
-    const dim3 grid(nv, chunks, c->g.nt);
-    if (pre)
-        hipLaunchKernelGGL((k_baryon_tensor_tri<2, 6>), grid, dim3(256), lds, c->stream, (const double2 *)evecs,
-                           (const double2 *)ph, nv, V3, tiles, (double2 *)T);
-    else
-        hipLaunchKernelGGL((k_baryon_tensor_tri<0, 0>), grid, dim3(256), lds, c->stream, (const double2 *)evecs,
-                           (const double2 *)ph, nv, V3, tiles, (double2 *)T);
+    const int low = nv / 2, high = nv - low, nt = c->g.nt;
+    const long pairs = (long)high * (high - 1) / 2;
+    if (pairs > 0) {
+        PairArgs P{(const double2 *)evecs, (const double2 *)ph, (double2 *)T, nv, nt, low, (int)((pairs + 63) / 64),
+                   ((nv + 15) / 16 + kPT - 1) / kPT, nt % 8 == 0, V3};
+        const long blocks = (long)nt * 2 * P.blocks * P.chunks;
+        LAPH_CHECK(blocks < (1L << 31), LAPH_EINVAL, "too many workgroups for one launch");
+        hipLaunchKernelGGL(k_baryon_tensor_pairs, dim3((unsigned)blocks), dim3(256), 0, c->stream, P);
+    }
     LAPH_HIP(hipGetLastError());
     LAPH_API_END(c)
 }
