@@ -152,69 +152,85 @@ __device__ __forceinline__ void acc_upper(Spin<A> &acc, const Cx<A> (&w0)[3], co
 struct HopCoef {
     double a0r, a0i, a1r, a1i, b2r, b2i, b3r, b3i;
 };
+__host__ __device__ constexpr HopCoef hop_coef(int mu)
+{
+    return mu == 0   ? HopCoef{0, 1, 0, 1, 0, -1, 0, -1}
+           : mu == 1 ? HopCoef{1, 0, -1, 0, -1, 0, 1, 0}
+           : mu == 2 ? HopCoef{0, 1, 0, -1, 0, -1, 0, 1}
+                     : HopCoef{-1, 0, -1, 0, -1, 0, -1, 0};
+}
 __device__ __forceinline__ Cx<double> unit_mul(double ur, double ui, Cx<double> z)
 {
     return {ur * z.re - ui * z.im, ur * z.im + ui * z.re};
+}
+
+// hop(o0, o1, q, sb, sw) gets the link of direction d times the two colour vectors of the
+// neighbour's projected half spinor, hop weight and boundary factor included, and what the
+// lower components take of them: acc2 += sb b2 (sw ? o1 : o0), acc3 += sb b3 (sw ? o0 : o1)
+template <bool O32, class F>
+__device__ __forceinline__ void hop_dir(const DslashArgs &P, int d, long i, int r, int x, int y, int z, int t, F hop)
+{
+    // (a table of the function's own: a shared one costs the rolled kernel 36 registers)
+    constexpr HopCoef kc[4] = {hop_coef(0), hop_coef(1), hop_coef(2), hop_coef(3)};
+    const int R = P.R, ns = P.ns, nt = P.nt, par = P.par;
+    const long Vh = P.Vh;
+    const double2 *in = (const double2 *)P.in;
+    const double2 *g = (const double2 *)P.gauge;
+    const int mu = d >> 1;
+    const bool fwd = !(d & 1);
+    const int st = fwd ? 1 : -1;
+    int xx = x, yy = y, zz = z, tt = t;
+    double w = mu == 3 ? P.wt : P.ws;
+    if (mu == 0) xx = (x + st + ns) % ns;
+    if (mu == 1) yy = (y + st + ns) % ns;
+    if (mu == 2) zz = (z + st + ns) % ns;
+    if (mu == 3) {
+        tt = (t + st + nt) % nt;
+        if (fwd ? t + 1 == nt : t == 0) w *= P.bct;
+    }
+    const long nb = lex_index(xx, yy, zz, tt, ns) >> 1;
+    Spin<double> s;
+    load_spinor<S64, O32>(in, nullptr, Vh, R, nb, r, s);
+    // U_mu(x), or for the backward hop U_mu(x - mu)^dag: planes read transposed, conjugated
+    const double2 *gp = g + (long)(mu * 2 + (fwd ? par : par ^ 1)) * 9 * Vh;
+    const long li = fwd ? i : nb;
+    const double cj = fwd ? 1.0 : -1.0;
+    Cx<double> U[9];
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+        const double2 v = elem<O32>(gp + (long)(fwd ? k : (k % 3) * 3 + k / 3) * Vh, li);
+        U[k] = {v.x, cj * v.y};
+    }
+    const HopCoef &q = kc[mu];
+    const double sa = fwd ? w : -w, sb = fwd ? 1.0 : -1.0;
+    const bool sw = mu < 2;
+    Cx<double> h0[3], h1[3], o0[3], o1[3];
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        h0[c] = w * s.v[0][c] + unit_mul(sa * q.a0r, sa * q.a0i, sw ? s.v[3][c] : s.v[2][c]);
+        h1[c] = w * s.v[1][c] + unit_mul(sa * q.a1r, sa * q.a1i, sw ? s.v[2][c] : s.v[3][c]);
+    }
+    mat_vec(U, h0, o0);
+    mat_vec(U, h1, o1);
+    hop(o0, o1, q, sb, sw);
 }
 
 template <bool O32>
 __device__ __forceinline__ void hop_rolled(const DslashArgs &P, long i, int r, int x, int y, int z, int t,
                                            Spin<double> &acc)
 {
-    constexpr HopCoef kc[4] = {{0, 1, 0, 1, 0, -1, 0, -1},
-                               {1, 0, -1, 0, -1, 0, 1, 0},
-                               {0, 1, 0, -1, 0, -1, 0, 1},
-                               {-1, 0, -1, 0, -1, 0, -1, 0}};
-    const int R = P.R, ns = P.ns, nt = P.nt, par = P.par;
-    const long Vh = P.Vh;
-    const double2 *in = (const double2 *)P.in;
-    const double2 *g = (const double2 *)P.gauge;
 #pragma unroll 1
-    for (int d = 0; d < 8; d++) {
-        const int mu = d >> 1;
-        const bool fwd = !(d & 1);
-        const int st = fwd ? 1 : -1;
-        int xx = x, yy = y, zz = z, tt = t;
-        double w = mu == 3 ? P.wt : P.ws;
-        if (mu == 0) xx = (x + st + ns) % ns;
-        if (mu == 1) yy = (y + st + ns) % ns;
-        if (mu == 2) zz = (z + st + ns) % ns;
-        if (mu == 3) {
-            tt = (t + st + nt) % nt;
-            if (fwd ? t + 1 == nt : t == 0) w *= P.bct;
-        }
-        const long nb = lex_index(xx, yy, zz, tt, ns) >> 1;
-        Spin<double> s;
-        load_spinor<S64, O32>(in, nullptr, Vh, R, nb, r, s);
-        // U_mu(x), or for the backward hop U_mu(x - mu)^dag: planes read transposed, conjugated
-        const double2 *gp = g + (long)(mu * 2 + (fwd ? par : par ^ 1)) * 9 * Vh;
-        const long li = fwd ? i : nb;
-        const double cj = fwd ? 1.0 : -1.0;
-        Cx<double> U[9];
+    for (int d = 0; d < 8; d++)
+        hop_dir<O32>(P, d, i, r, x, y, z, t,
+                     [&](const Cx<double> (&o0)[3], const Cx<double> (&o1)[3], const HopCoef &q, double sb, bool sw) {
 #pragma unroll
-        for (int k = 0; k < 9; k++) {
-            const double2 v = elem<O32>(gp + (long)(fwd ? k : (k % 3) * 3 + k / 3) * Vh, li);
-            U[k] = {v.x, cj * v.y};
-        }
-        const HopCoef &q = kc[mu];
-        const double sa = fwd ? w : -w, sb = fwd ? 1.0 : -1.0;
-        const bool sw = mu < 2;
-        Cx<double> h0[3], h1[3], o0[3], o1[3];
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            h0[c] = w * s.v[0][c] + unit_mul(sa * q.a0r, sa * q.a0i, sw ? s.v[3][c] : s.v[2][c]);
-            h1[c] = w * s.v[1][c] + unit_mul(sa * q.a1r, sa * q.a1i, sw ? s.v[2][c] : s.v[3][c]);
-        }
-        mat_vec(U, h0, o0);
-        mat_vec(U, h1, o1);
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            acc.v[0][c] = acc.v[0][c] + o0[c];
-            acc.v[1][c] = acc.v[1][c] + o1[c];
-            acc.v[2][c] = acc.v[2][c] + unit_mul(sb * q.b2r, sb * q.b2i, sw ? o1[c] : o0[c]);
-            acc.v[3][c] = acc.v[3][c] + unit_mul(sb * q.b3r, sb * q.b3i, sw ? o0[c] : o1[c]);
-        }
-    }
+            for (int c = 0; c < 3; c++) {
+                acc.v[0][c] = acc.v[0][c] + o0[c];
+                acc.v[1][c] = acc.v[1][c] + o1[c];
+                acc.v[2][c] = acc.v[2][c] + unit_mul(sb * q.b2r, sb * q.b2i, sw ? o1[c] : o0[c]);
+                acc.v[3][c] = acc.v[3][c] + unit_mul(sb * q.b3r, sb * q.b3i, sw ? o0[c] : o1[c]);
+            }
+        });
 }
 
 // checkerboard index and coordinates of position pos of the tiled site walk: tiles of
@@ -329,6 +345,113 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
     store_spinor<SP, O32>((typename SP::E *)P.out, P.out_nrm, Vh, R, i, r, res);
 }
 
+// The FP64 hop of launches with few (site, right-hand side) pairs: the rolled kernel above
+// walks eight directions one memory latency after the other, which is what bounds it while
+// the chip is not full (12 us for the 256 sites of one parity of 4^3 x 8, 5 us here).  Here a workgroup
+// takes 64 pairs with one wave per direction, so all eight neighbours are read at once; the
+// products go through LDS, and waves 0 and 1 add them up in direction order and apply the
+// clover epilogue to one chirality each (their clover block is loaded ahead of the barrier).
+constexpr int kSplit = 64;
+
+template <int MODE, bool O32>
+__global__ __launch_bounds__(8 * kSplit) void k_dslash_split(const DslashArgs P)
+{
+    __shared__ double2 ex[8][6][kSplit];
+    const int d = __builtin_amdgcn_readfirstlane(threadIdx.x / kSplit), l = threadIdx.x & (kSplit - 1);
+    const int R = P.R;
+    const long Vh = P.Vh;
+    const long tid = (long)xcd_block(blockIdx.x, gridDim.x) * kSplit + l;
+    const bool valid = tid < Vh * R;
+    const unsigned pos = (unsigned)tid / (unsigned)R;
+    const long i = valid ? pos : 0;
+    const int r = valid ? (int)((unsigned)tid - pos * (unsigned)R) : 0;
+    int x, y, z, t;
+    cb_coords(i, P.par, P.ns, x, y, z, t);
+    hop_dir<O32>(P, d, i, r, x, y, z, t,
+                 [&](const Cx<double> (&o0)[3], const Cx<double> (&o1)[3], const HopCoef &, double, bool) {
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            ex[d][c][l] = make_double2(o0[c].re, o0[c].im);
+            ex[d][3 + c][l] = make_double2(o1[c].re, o1[c].im);
+        }
+    });
+    constexpr bool kClov = MODE != M_PLAIN;
+    double cl[36];
+    if (d < 2) {
+        if constexpr (kClov) {
+#pragma unroll
+            for (int k = 0; k < 36; k++) cl[k] = elem<O32>((const double *)P.clov + (long)(d * 36 + k) * Vh, i);
+        }
+    }
+    __syncthreads();
+    if (d >= 2 || !valid) return;
+    Cx<double> acc[6], xv[6];
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        acc[k] = xv[k] = {0.0, 0.0};
+        if (P.x) {
+            const double2 e = elem<O32>((const double2 *)P.x + (long)(d * 6 + k) * Vh * R, i * R + r);
+            xv[k] = {e.x, e.y};
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+        constexpr HopCoef kc[4] = {hop_coef(0), hop_coef(1), hop_coef(2), hop_coef(3)};
+        const HopCoef &q = kc[e >> 1];
+        const double sb = (e & 1) ? -1.0 : 1.0;
+        // wave 0 adds o0 and o1, wave 1 what the lower components take of them
+        const int f = d && e < 4 ? 3 : 0;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const double2 a = ex[e][f + c][l], b = ex[e][3 - f + c][l];
+            const Cx<double> u = {a.x, a.y}, v = {b.x, b.y};
+            acc[c] = acc[c] + (d ? unit_mul(sb * q.b2r, sb * q.b2i, u) : u);
+            acc[3 + c] = acc[3 + c] + (d ? unit_mul(sb * q.b3r, sb * q.b3i, v) : v);
+        }
+    }
+    if (P.g5d && d) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) acc[k] = cneg(acc[k]);
+    }
+    auto herm = [&](const Cx<double> (&v)[6], Cx<double> (&o)[6]) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) o[k] = cl[k] * v[k];
+        int e = 6;
+#pragma unroll
+        for (int a = 1; a < 6; a++)
+#pragma unroll
+            for (int c = 0; c < a; c++) {
+                const Cx<double> L = {cl[e], cl[e + 1]};
+                e += 2;
+                o[a] = o[a] + L * v[c];
+                o[c] = o[c] + conjmul(L, v[a]);
+            }
+    };
+    const double ca = P.a, cc = P.c;
+    Cx<double> res[6];
+    if constexpr (MODE == M_PLAIN || MODE == M_INV_AFTER) {
+        Cx<double> m[6];
+        if constexpr (MODE == M_INV_AFTER) herm(acc, m);
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            res[k] = cc * (MODE == M_INV_AFTER ? m[k] : acc[k]);
+            if (P.x) res[k] = res[k] + ca * xv[k];
+        }
+    } else if constexpr (MODE == M_INV_OF_SUM) {
+        Cx<double> sum[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) sum[k] = ca * xv[k] + cc * acc[k];
+        herm(sum, res);
+    } else {  // M_CLOV_ADD
+        herm(xv, res);
+#pragma unroll
+        for (int k = 0; k < 6; k++) res[k] = res[k] + cc * acc[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 6; k++)
+        elem<O32>((double2 *)P.out + (long)(d * 6 + k) * Vh * R, i * R + r) = make_double2(res[k].re, res[k].im);
+}
+
 template <class SP, class CP>
 __global__ __launch_bounds__(256) void k_clover_apply(const typename CP::E *__restrict__ cl,
                                                        const typename SP::E *__restrict__ x, const float *x_nrm,
@@ -376,6 +499,23 @@ void launch_modes(int mode, dim3 grid, dim3 block, hipStream_t st, const DslashA
     }
 }
 
+// pairs up to which the split kernel is the faster one (per launch, rolled against split):
+// 256: 11.7 / 5.0 us, 4096: 12.2 / 5.9, 13824: 14.8 / 7.7, 32768: 16.2 / 15.0; with 65536 it is
+// 3% behind, with 131072 (R = 32) 28 / 33 us
+constexpr long kSplitMost = 32768;
+
+template <bool O32>
+void launch_split(int mode, long n, hipStream_t st, const DslashArgs &a)
+{
+    const dim3 grid(nblocks_for(n, kSplit)), block(8 * kSplit);
+    switch (mode) {
+    case M_PLAIN: hipLaunchKernelGGL((k_dslash_split<M_PLAIN, O32>), grid, block, 0, st, a); break;
+    case M_INV_AFTER: hipLaunchKernelGGL((k_dslash_split<M_INV_AFTER, O32>), grid, block, 0, st, a); break;
+    case M_INV_OF_SUM: hipLaunchKernelGGL((k_dslash_split<M_INV_OF_SUM, O32>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((k_dslash_split<M_CLOV_ADD, O32>), grid, block, 0, st, a); break;
+    }
+}
+
 template <class SP, class GP, class CP>
 void launch_dslash(laph_ctx *c, int mode, const DslashArgs &a, hipStream_t st)
 {
@@ -393,7 +533,10 @@ void launch_dslash(laph_ctx *c, int mode, const DslashArgs &a, hipStream_t st)
     DslashArgs b = a;
     b.wby = b.wbz = 0;
     if (a.R >= 8) b.wby = b.wbz = (a.ns % 3 == 0) ? 3 : 2;
-    launch_modes<SP, GP, CP, true>(mode, grid, block, st, b);
+    if (n <= kSplitMost)
+        launch_split<true>(mode, n, st, b);
+    else
+        launch_modes<SP, GP, CP, true>(mode, grid, block, st, b);
     LAPH_HIP(hipGetLastError());
     bool has_x = a.x != nullptr && (mode != M_PLAIN || a.x);
     if (e0)
