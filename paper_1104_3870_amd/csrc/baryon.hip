@@ -34,60 +34,17 @@ struct Zgemm {
 struct GemmS {
     Zgemm g;
     int M, N, K;
-    __device__ bool tile(long &bt, int &m0, int &n0) const
-    {
-        bt = blockIdx.z;
-        m0 = blockIdx.x * zg::kTM;
-        n0 = blockIdx.y * zg::kTN;
-        return true;
-    }
-    // element q of a lane: e = lane + 256 q; the index running along the operand's unit
-    // stride varies fastest across lanes
-    template <int KT>
-    struct Reg {
-        double2 a[zg::kPer<KT>], b[zg::kPer<KT>];
-    };
-    template <int KT>
-    __device__ void am(int e, int &m, int &k) const
-    {
-        const bool ak = g.sAk == 1;
-        m = ak ? e / KT : e % zg::kTM;
-        k = ak ? e % KT : e / zg::kTM;
-    }
-    template <int KT>
-    __device__ void load(Reg<KT> &r, long bt, int m0, int n0, int k0) const
+    int tiles_m, tiles_n;
+    long batches;
+    __device__ zg::Side a(long bt) const
     {
         const long bo = bt / g.nbi, bi = bt - bo * g.nbi;
-        const double2 *A = g.A + bo * g.sAo + bi * g.sAi;
-        const double2 *B = g.B + bo * g.sBo + bi * g.sBi;
-#pragma unroll
-        for (int q = 0; q < zg::kPer<KT>; q++) {
-            const int e = threadIdx.x + 256 * q;
-            int m, k;
-            am<KT>(e, m, k);
-            // explicit branches (a select against a local zero would load through a flat
-            // address)
-            r.a[q] = r.b[q] = make_double2(0.0, 0.0);
-            if (m0 + m < M && k0 + k < K) r.a[q] = A[(m0 + m) * g.sAm + (long)(k0 + k) * g.sAk];
-            const int n = e % zg::kTN, kb = e / zg::kTN;
-            if (n0 + n < N && k0 + kb < K) r.b[q] = B[(long)(k0 + kb) * g.sBk + (n0 + n) * g.sBn];
-        }
+        return {g.A + bo * g.sAo + bi * g.sAi, g.sAm, g.sAk, M, g.conjA, nullptr};
     }
-    template <int KT>
-    __device__ void put(zg::Tile<KT> &t, const Reg<KT> &r) const
+    __device__ zg::Side b(long bt) const
     {
-        const double sg = g.conjA ? -1.0 : 1.0;
-#pragma unroll
-        for (int q = 0; q < zg::kPer<KT>; q++) {
-            const int e = threadIdx.x + 256 * q;
-            int m, k;
-            am<KT>(e, m, k);
-            t.ar[k][m] = r.a[q].x;
-            t.ai[k][m] = sg * r.a[q].y;
-            const int n = e % zg::kTN, kb = e / zg::kTN;
-            t.br[kb][n] = r.b[q].x;
-            t.bi[kb][n] = r.b[q].y;
-        }
+        const long bo = bt / g.nbi, bi = bt - bo * g.nbi;
+        return {g.B + bo * g.sBo + bi * g.sBi, g.sBn, g.sBk, N, 0, nullptr};
     }
     __device__ void store(long bt, int m, int n, double re, double im) const
     {
@@ -99,10 +56,11 @@ struct GemmS {
 void zgemm(laph_ctx *c, const Zgemm &g, long batch)
 {
     if (g.M <= 0 || g.N <= 0 || batch <= 0) return;
-    const unsigned gm = (g.M + zg::kTM - 1) / zg::kTM, gn = (g.N + zg::kTN - 1) / zg::kTN;
-    LAPH_CHECK(gn <= 65535 && batch <= 65535, LAPH_EINVAL, "product too large for one launch");
-    GemmS s{g, g.M, g.N, g.K};
-    hipLaunchKernelGGL((zg::k_zgemm<16, GemmS>), dim3(gm, gn, (unsigned)batch), dim3(256), 0, c->stream, s);
+    const int gm = (g.M + zg::kTM - 1) / zg::kTM, gn = (g.N + zg::kTN - 1) / zg::kTN;
+    GemmS s{g, g.M, g.N, g.K, gm, gn, batch};
+    LAPH_CHECK(gn <= 65535 && batch <= 65535 && zg::grid_of(s) < (1L << 31), LAPH_EINVAL,
+               "product too large for one launch");
+    hipLaunchKernelGGL((zg::k_zgemm<8, false, false, GemmS>), dim3((unsigned)zg::grid_of(s)), dim3(256), 0, c->stream, s);
     LAPH_HIP(hipGetLastError());
 }
 

@@ -88,59 +88,19 @@ __global__ void k_phase(double2 *ph, int ns, int k0, int k1, int k2)
 }
 
 // O[t][n][m] = sum_{x, c} conj(a[t][n][x][c]) ph[x] b[t][m][x][c]: per slice the product
-// A^dag (ph B) over K = 3 Ns^3 on the FP64 matrix cores; one block per slice and 64 x 64
-// tile, the conjugate and the phase applied while staging
+// A^dag (ph B) over K = 3 Ns^3 on the FP64 matrix cores, the conjugate and the phase applied
+// while staging
 struct OverlapS {
-    const double2 *a, *b, *ph;
+    const double2 *pa, *pb, *ph;
     double2 *out;
     int M, N, K;  // na, nb, 3 Ns^3
-    __device__ bool tile(long &bt, int &m0, int &n0) const
+    int tiles_m, tiles_n;
+    long batches;
+    __device__ zg::Side a(long t) const { return {pa + t * M * (long)K, K, 1, M, 1, nullptr}; }
+    __device__ zg::Side b(long t) const { return {pb + t * N * (long)K, K, 1, N, 0, ph}; }
+    __device__ void store(long t, int m, int n, double re, double im) const
     {
-        bt = blockIdx.z;
-        m0 = blockIdx.x * zg::kTM;
-        n0 = blockIdx.y * zg::kTN;
-        return true;
-    }
-    // element q of a lane: e = lane + 256 q, row r = e / KT, k = e % KT (k fastest: KT
-    // consecutive values of a row)
-    template <int KT>
-    struct Reg {
-        double2 a[zg::kPer<KT>], b[zg::kPer<KT>], p[zg::kPer<KT>];
-    };
-    template <int KT>
-    __device__ void load(Reg<KT> &g, long bt, int m0, int n0, int k0) const
-    {
-        static_assert(zg::kTM == zg::kTN, "one loop stages both operands");
-#pragma unroll
-        for (int q = 0; q < zg::kPer<KT>; q++) {
-            const int e = threadIdx.x + 256 * q, r = e / KT, k = e - r * KT;
-            const long kk = (long)k0 + k;
-            // (explicit branches: a select between a global and a local zero would become a
-            // select of addresses and a flat load)
-            g.a[q] = g.b[q] = g.p[q] = make_double2(0.0, 0.0);
-            if (kk < K) {
-                if (m0 + r < M) g.a[q] = a[(bt * M + m0 + r) * (long)K + kk];
-                if (n0 + r < N) g.b[q] = b[(bt * N + n0 + r) * (long)K + kk];
-                g.p[q] = ph[kk / 3];
-            }
-        }
-    }
-    template <int KT>
-    __device__ void put(zg::Tile<KT> &t, const Reg<KT> &g) const
-    {
-#pragma unroll
-        for (int q = 0; q < zg::kPer<KT>; q++) {
-            const int e = threadIdx.x + 256 * q, r = e / KT, k = e - r * KT;
-            const double2 vb = cmul(g.p[q], g.b[q]);
-            t.ar[k][r] = g.a[q].x;
-            t.ai[k][r] = -g.a[q].y;
-            t.br[k][r] = vb.x;
-            t.bi[k][r] = vb.y;
-        }
-    }
-    __device__ void store(long bt, int m, int n, double re, double im) const
-    {
-        out[(bt * M + m) * (long)N + n] = make_double2(re, im);
+        out[(t * M + m) * (long)N + n] = make_double2(re, im);
     }
 };
 
@@ -182,11 +142,12 @@ void overlap_slices(laph_ctx *c, const double2 *a, int na, const double2 *b, int
 {
     const long V3 = c->g.V3;
     hipLaunchKernelGGL(k_phase, dim3(nblocks_for(V3, 256)), dim3(256), 0, c->stream, phase, c->g.ns, k0, k1, k2);
-    const unsigned gn = (na + zg::kTM - 1) / zg::kTM, gm = (nb + zg::kTN - 1) / zg::kTN;
+    const int gn = (na + zg::kTM - 1) / zg::kTM, gm = (nb + zg::kTN - 1) / zg::kTN;
     LAPH_CHECK(gm <= 65535 && c->g.nt <= 65535, LAPH_EINVAL, "too many fields for one launch");
     LAPH_CHECK(3 * V3 < (1L << 31), LAPH_EINVAL, "slice too large");
-    OverlapS os{a, b, phase, out, na, nb, (int)(3 * V3)};
-    hipLaunchKernelGGL((zg::k_zgemm<16, OverlapS>), dim3(gn, gm, c->g.nt), dim3(256), 0, c->stream, os);
+    OverlapS os{a, b, phase, out, na, nb, (int)(3 * V3), gn, gm, c->g.nt};
+    LAPH_CHECK(zg::grid_of(os) < (1L << 31), LAPH_EINVAL, "too many fields for one launch");
+    hipLaunchKernelGGL((zg::k_zgemm<12, true, true, OverlapS>), dim3((unsigned)zg::grid_of(os)), dim3(256), 0, c->stream, os);
     LAPH_HIP(hipGetLastError());
 }
 
