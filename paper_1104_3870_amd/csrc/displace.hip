@@ -16,13 +16,25 @@ namespace {
 // out[t][j][x] = (D v_j)(x) for colour fields in the eigenvector layout [Nt][n][Ns^3][3]:
 // one lane per site (t, x) forms the path's link product W(x) once (W = U(x) U(x+e) ...
 // U(x+(len-1)e), or the product of the adjoints backwards) and applies it to v_j at the
-// far end for every j, so each link is read once per site, not once per vector
-__global__ void k_displace(const double2 *__restrict__ U, const double2 *__restrict__ v, double2 *__restrict__ out,
+// far end for every j, so each link is read once per site, not once per vector.  Bound by
+// HBM.  A lane's result is 48 bytes, and storing it as three 16-byte pieces makes three
+// partial writes of every cache line: a wave instead passes its 64 sites through LDS (its
+// own 3 KB a vector, no barrier) and stores whole lines past the caches.  112 vectors on
+// 24^3 x 128, three links: 3.75 ms (5.3 TB/s), with partial stores 4.6 ms; two or one vector
+// in flight 3.77-3.8 ms.
+constexpr int kDisLanes = 256, kDisVecs = 4;
+typedef double vd2 __attribute__((ext_vector_type(2)));
+
+__global__ __launch_bounds__(kDisLanes) void k_displace(const double2 *__restrict__ U, const double2 *__restrict__ v, double2 *__restrict__ out,
                            int ns, int nt, int n, int dir, int sign, int len)
 {
-    const long V3 = (long)ns * ns * ns;
-    const long q = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (q >= (long)nt * V3) return;
+    __shared__ double2 pass[kDisLanes / 64][kDisVecs][192];
+    const long V3 = (long)ns * ns * ns, sites = (long)nt * V3;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+    const long q0 = blockIdx.x * (long)kDisLanes + 64 * wave;  // the wave's first site
+    if (q0 >= sites) return;
+    // (lanes past the end work on the last site and store nothing)
+    const long q = min(q0 + lane, sites - 1);
     const int t = (int)(q / V3);
     const long xyz = q - (long)t * V3;
     int c[3] = {(int)(xyz % ns), (int)((xyz / ns) % ns), (int)(xyz / ((long)ns * ns))};
@@ -61,15 +73,43 @@ __global__ void k_displace(const double2 *__restrict__ U, const double2 *__restr
     int f[3] = {c[0], c[1], c[2]};
     f[dir] = cur;
     const long far = f[0] + (long)ns * (f[1] + (long)ns * f[2]);
-    // four vectors' loads in flight per lane (each lane streams all n vectors of its site)
-#pragma unroll 4
-    for (int j = 0; j < n; j++) {
-        const double2 *vf = v + (((long)t * n + j) * V3 + far) * 3;
-        const double2 w0 = vf[0], w1 = vf[1], w2 = vf[2];
-        double2 *o = out + (((long)t * n + j) * V3 + xyz) * 3;
+    // the lane's three elements of the wave's 192 contiguous ones (site e / 3, colour e % 3)
+    long to[3];
 #pragma unroll
-        for (int a = 0; a < 3; a++)
-            o[a] = cadd(cadd(cmul(W[a * 3], w0), cmul(W[a * 3 + 1], w1)), cmul(W[a * 3 + 2], w2));
+    for (int k = 0; k < 3; k++) {
+        const int e = lane + 64 * k;
+        const long s = q0 + e / 3, ts = s / V3;
+        to[k] = s < sites ? (ts * n * V3 + (s - ts * V3)) * 3 + e % 3 : -1;
+    }
+    const double2 *vf = v + ((long)t * n * V3 + far) * 3;
+    // kDisVecs vectors' loads in flight per lane
+    for (int j0 = 0; j0 < n; j0 += kDisVecs) {
+        double2 w[kDisVecs][3];
+#pragma unroll
+        for (int u = 0; u < kDisVecs; u++)
+#pragma unroll
+            for (int a = 0; a < 3; a++) w[u][a] = vf[(long)min(j0 + u, n - 1) * V3 * 3 + a];
+#pragma unroll
+        for (int u = 0; u < kDisVecs; u++) {
+            double2 *row = pass[wave][u];
+#pragma unroll
+            for (int a = 0; a < 3; a++)
+                row[3 * lane + a] = cadd(cadd(cmul(W[a * 3], w[u][0]), cmul(W[a * 3 + 1], w[u][1])),
+                                         cmul(W[a * 3 + 2], w[u][2]));
+        }
+        // the wave's lanes read each other's values (LDS keeps a wave's order; this keeps the compiler's)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int u = 0; u < kDisVecs; u++) {
+            if (j0 + u >= n) break;
+            double2 *o = out + (long)(j0 + u) * V3 * 3;
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                const double2 r = pass[wave][u][lane + 64 * k];
+                if (to[k] >= 0) __builtin_nontemporal_store(vd2{r.x, r.y}, (vd2 *)&o[to[k]]);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -131,7 +171,7 @@ extern "C" int laph_displace(laph_ctx_t c, const double *U, int dir, int sign, i
     LAPH_CHECK(dir >= 0 && dir < 3 && (sign == 1 || sign == -1) && length >= 0, LAPH_EINVAL,
                "direction 0..2, sign +-1, length >= 0");
     const long total = (long)c->g.nt * c->g.V3;
-    hipLaunchKernelGGL(k_displace, dim3(nblocks_for(total, 256)), dim3(256), 0, c->stream, (const double2 *)U,
+    hipLaunchKernelGGL(k_displace, dim3(nblocks_for(total, kDisLanes)), dim3(kDisLanes), 0, c->stream, (const double2 *)U,
                        (const double2 *)v, (double2 *)out, c->g.ns, c->g.nt, n, dir, sign, length);
     LAPH_HIP(hipGetLastError());
     LAPH_API_END(c)
