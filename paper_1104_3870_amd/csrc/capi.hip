@@ -190,7 +190,6 @@ extern "C" int laph_destroy(laph_ctx_t c)
     (void)hipStreamSynchronize(c->stream);
     cache_release_all(c);
     scratch_reset(c);
-    if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->pin) (void)hipHostFree(c->pin);
     for (hipEvent_t e : c->pin_ev)
         if (e) (void)hipEventDestroy(e);

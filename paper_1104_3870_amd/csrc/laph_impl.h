@@ -187,7 +187,6 @@ struct laph_ctx {
     // tiled walk, tile_override > 0 fixes the sites per block
     int walk_mode = 0;
     int tile_override = 0;
-    hipStream_t cap_stream = nullptr;  // capture stream for HIP graphs (default priority)
     // pinned two-slot readback of the per-RHS Krylov scalars and the events marking each
     // slot's copy (the CG loop reads the previous iteration's slot without draining the queue)
     void *pin = nullptr;

@@ -555,22 +555,6 @@ __global__ __launch_bounds__(kBS) void k_normsq(Vec a, long Vh, int R, double *p
     block_partial<1>(acc, R, partial);
 }
 
-// alpha = rho / |q|^2
-// deterministic sum of right-hand-side-major partials partial[r * nblk + b]
-__device__ __forceinline__ double sum_partials_rmajor(const double *partial, int nblk, int r)
-{
-    __shared__ double lds[kBS];
-    double v = 0;
-    for (int b = threadIdx.x; b < nblk; b += kBS) v += partial[(long)r * nblk + b];
-    lds[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kBS / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) lds[threadIdx.x] += lds[threadIdx.x + s];
-        __syncthreads();
-    }
-    return lds[0];
-}
-
 // partial[b][row] (nrow values per block, block-major as the fused epilogues write them)
 // -> out[row][kChunks], chunk ch = fixed-order sum of its contiguous share of the blocks
 // (the first stage of a deterministic two-stage reduction; nrow <= kBS)
@@ -606,6 +590,45 @@ __global__ __launch_bounds__(kBS) void k_prereduce(const double *partial, int nb
     }
 }
 
+// The second stage: what lane t adds of one row of partials before the sum over the block's
+// lanes.  Prereduced: in[row][nchunk].  kDirect: nblk <= kChunks block-major partials as the
+// epilogues wrote them, with the first stage left out: a chunk of it holds one block or none,
+// so both routes add the same values in the same order, and the first stage would be a launch
+// that only transposes.
+template <bool kDirect>
+__device__ __forceinline__ double row_part(const double *in, int nblk, int nrow, int row)
+{
+    double e[kChunks / kBS], v = 0;
+#pragma unroll
+    for (int j = 0; j < kChunks / kBS; j++) {  // (unconditional: all loads in flight)
+        const int ch = threadIdx.x + j * kBS;
+        if constexpr (kDirect) {
+            const int beg = (int)((long)nblk * ch / kChunks), end = (int)((long)nblk * (ch + 1) / kChunks);
+            e[j] = in[(long)min(beg, nblk - 1) * nrow + row];
+            if (beg == end) e[j] = 0;
+        } else {
+            e[j] = in[(long)row * kChunks + ch];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kChunks / kBS; j++) v += e[j];
+    return v;
+}
+
+// deterministic sum over the one row of right-hand side r
+template <bool kDirect>
+__device__ __forceinline__ double sum_row(const double *in, int nblk, int R, int r)
+{
+    __shared__ double lds[kBS];
+    lds[threadIdx.x] = row_part<kDirect>(in, nblk, R, r);
+    __syncthreads();
+    for (int s = kBS / 2; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) lds[threadIdx.x] += lds[threadIdx.x + s];
+        __syncthreads();
+    }
+    return lds[0];
+}
+
 // ------------------------------------------------- fused multi-RHS BiCGStab (Sec. IV)
 // The low-precision BiCGStab iteration takes its inner products <r0, v>, <t, s>, |t|^2 from
 // the epilogues of the hops that form v = M p and t = M s (M_INV_AFTER_DOT), and keeps its
@@ -639,16 +662,13 @@ __device__ __forceinline__ void add_bs_steps(const BsDirs &d, int n, const Scal 
     }
 }
 
-// the three value rows of right-hand side r in prereduced partials [(e R + r) * nblk + b]
-__device__ __forceinline__ void sum_rows3(const double *partial, int nblk, int R, int r, double (&out)[3])
+// the three value rows (e R + r) of right-hand side r
+template <bool kDirect>
+__device__ __forceinline__ void sum_rows3(const double *in, int nblk, int R, int r, double (&out)[3])
 {
     __shared__ double lds[3][kBS];
-    double v[3] = {0, 0, 0};
-    for (int b = threadIdx.x; b < nblk; b += kBS)
 #pragma unroll
-        for (int e = 0; e < 3; e++) v[e] += partial[((long)e * R + r) * nblk + b];
-#pragma unroll
-    for (int e = 0; e < 3; e++) lds[e][threadIdx.x] = v[e];
+    for (int e = 0; e < 3; e++) lds[e][threadIdx.x] = row_part<kDirect>(in, nblk, 3 * R, e * R + r);
     __syncthreads();
     for (int h = kBS / 2; h > 0; h >>= 1) {
         if ((int)threadIdx.x < h)
@@ -662,11 +682,12 @@ __device__ __forceinline__ void sum_rows3(const double *partial, int nblk, int R
 
 // alpha = rho / <r0, v> from the epilogue partials of v = M p; the previous alpha and
 // omega move into the step history first
-__global__ void k_fin_bs_alpha(const double *partial, int nblk, int R, Scal *sc)
+template <bool kDirect>
+__global__ __launch_bounds__(kBS) void k_fin_bs_alpha(const double *partial, int nblk, int R, Scal *sc)
 {
     const int r = blockIdx.x;
     double s[3];
-    sum_rows3(partial, nblk, R, r, s);
+    sum_rows3<kDirect>(partial, nblk, R, r, s);
     if (threadIdx.x) return;
     Scal &q = sc[r];
     if (!q.active) {
@@ -690,11 +711,12 @@ __global__ void k_fin_bs_alpha(const double *partial, int nblk, int R, Scal *sc)
 }
 
 // omega = <t, s> / |t|^2 from the epilogue partials of t = M s, which hold <s, t> = conj <t, s>
-__global__ void k_fin_bs_omega(const double *partial, int nblk, int R, Scal *sc)
+template <bool kDirect>
+__global__ __launch_bounds__(kBS) void k_fin_bs_omega(const double *partial, int nblk, int R, Scal *sc)
 {
     const int r = blockIdx.x;
     double s[3];
-    sum_rows3(partial, nblk, R, r, s);
+    sum_rows3<kDirect>(partial, nblk, R, r, s);
     if (threadIdx.x) return;
     Scal &q = sc[r];
     if (!q.active) {
@@ -751,15 +773,20 @@ __global__ __launch_bounds__(kBS) void k_bs_r(Vec s, Vec t, Vec r, Vec r0, long 
     }
 }
 
-// rho_new = <r0, r>, beta = (rho_new / rho)(alpha / omega), |r|^2 from the prereduced
-// partials of k_bs_r
-__global__ void k_fin_bs_beta(const double *partial, int nblk, int R, Scal *sc)
+// The iteration's scalars as its last finalisation leaves them, stored to the host's slot by
+// the kernel itself: a copy command between the kernels leaves the device idle for about 12 us
+// on either side of it (25 of the 100 us of a CG iteration on 8^3 x 16 with 32 right-hand sides)
+__device__ __forceinline__ void send_scal(const Scal &q, Scal *pin)
 {
-    const int r = blockIdx.x;
-    double s[3];
-    sum_rows3(partial, nblk, R, r, s);
-    if (threadIdx.x) return;
-    Scal &q = sc[r];
+    static_assert(sizeof(Scal) % 8 == 0 && sizeof(Scal) / 8 <= kBS, "one 8-byte word per lane");
+    __syncthreads();
+    if (pin && threadIdx.x < sizeof(Scal) / 8) ((double *)pin)[threadIdx.x] = ((const double *)&q)[threadIdx.x];
+}
+
+// rho_new = <r0, r>, beta = (rho_new / rho)(alpha / omega), |r|^2 from the partials of
+// k_bs_r; a copy of the scalars to pin
+__device__ __forceinline__ void set_bs_beta(const double (&s)[3], Scal &q)
+{
     if (!q.active) {
         q.beta = make_double2(0, 0);
         return;
@@ -776,6 +803,16 @@ __global__ void k_fin_bs_beta(const double *partial, int nblk, int R, Scal *sc)
     }
     q.beta = cmul(cdiv(rn, q.rho), cdiv(q.alpha, q.omega));
     q.rho = rn;
+}
+
+template <bool kDirect>
+__global__ __launch_bounds__(kBS) void k_fin_bs_beta(const double *partial, int nblk, int R, Scal *sc, Scal *pin)
+{
+    const int r = blockIdx.x;
+    double s[3];
+    sum_rows3<kDirect>(partial, nblk, R, r, s);
+    if (threadIdx.x == 0) set_bs_beta(s, sc[r]);
+    send_scal(sc[r], pin + r);
 }
 
 // pout = r + beta (p - omega v) with p = d.p[0]; pout may be d.p[0] or, when the owed steps
@@ -865,13 +902,18 @@ __global__ void k_bs_drop(Scal *sc, int R, unsigned mask)
     }
 }
 
-// rmajor: partials of the fused hopping epilogue (one value per block and RHS)
-__global__ void k_fin_cg_alpha(const double *partial, int nblk, int R, Scal *sc, int rmajor)
+// where the CG scalars come from: block_partial's values, or the fused hopping epilogue's
+// partials (one value per block and RHS), prereduced or as written
+enum { kFromBlocks, kFromPre, kFromHop };
+
+// alpha = rho / |q|^2
+template <int kFrom>
+__global__ __launch_bounds__(kBS) void k_fin_cg_alpha(const double *partial, int nblk, int R, Scal *sc)
 {
     int r = blockIdx.x;
     double s[1];
-    if (rmajor)
-        s[0] = sum_partials_rmajor(partial, nblk, r);
+    if constexpr (kFrom != kFromBlocks)
+        s[0] = sum_row<kFrom == kFromHop>(partial, nblk, R, r);
     else
         sum_partials<1>(partial, nblk, R, r, s);
     if (threadIdx.x) return;
@@ -936,19 +978,8 @@ __global__ __launch_bounds__(kBS) void k_cg_update(Vec x, Vec p, Vec res, Vec q,
 
 // beta = |r|^2 / rho; rho = |r|^2; r2 = |res|^2; with hi_conv the recursive even-odd
 // residual alone may declare convergence (plain FP64 iteration)
-__global__ void k_fin_cg_beta(const double *partial, int nblk, int R, Scal *sc, int hi_conv, int recur,
-                              int rmajor)
+__device__ __forceinline__ void set_cg_beta(const double (&s)[2], Scal &q, int hi_conv, int recur)
 {
-    int r = blockIdx.x;
-    double s[2];
-    if (rmajor) {
-        s[0] = sum_partials_rmajor(partial, nblk, r);
-        s[1] = 0.0;
-    } else {
-        sum_partials<2>(partial, nblk, R, r, s);
-    }
-    if (threadIdx.x) return;
-    Scal &q = sc[r];
     if (!q.active) {
         q.beta = make_double2(0, 0);
         return;
@@ -966,6 +997,23 @@ __global__ void k_fin_cg_beta(const double *partial, int nblk, int R, Scal *sc, 
     q.rho_prev = q.rho.x;
     q.rho = make_double2(s[0], 0);
     if (hi_conv && (s[1] <= q.tol2 || !(s[0] > 0))) q.active = 0;
+}
+
+// (pin: a copy of the scalars for the host, or null)
+template <int kFrom>
+__global__ __launch_bounds__(kBS) void k_fin_cg_beta(const double *partial, int nblk, int R, Scal *sc, int hi_conv,
+                                                     int recur, Scal *pin)
+{
+    int r = blockIdx.x;
+    double s[2];
+    if constexpr (kFrom != kFromBlocks) {
+        s[0] = sum_row<kFrom == kFromHop>(partial, nblk, R, r);
+        s[1] = 0.0;
+    } else {
+        sum_partials<2>(partial, nblk, R, r, s);
+    }
+    if (threadIdx.x == 0) set_cg_beta(s, sc[r], hi_conv, recur);
+    send_scal(sc[r], pin ? pin + r : nullptr);
 }
 
 // direction update pout = r + beta d_0 (real beta); pout may be d_0, the oldest direction
@@ -1283,7 +1331,6 @@ struct Work {
     int R;
     Scal *sc;      // device
     double *part;  // device partials [kMaxBlocks][R][4]
-    bool use_graph = false;  // capture the CG iteration body in a HIP graph
     double delta2 = 0.01;    // reliable update when |res|^2 fell below delta2 times its last FP64 value
     int dirs = 0;            // direction buffers of the fused CG loop (0: the default)
     bool x_zero = false;     // x_hi is known to be zero (the first residual is bhat itself)
@@ -1313,6 +1360,20 @@ void launch_fin(laph_ctx *c, K kern, int R, Args... args)
 {
     hipLaunchKernelGGL(kern, dim3(R), dim3(kBS), 0, c->stream, args...);
     LAPH_HIP(hipGetLastError());
+}
+
+// the scalars from block-major partials of nrow values each: through k_prereduce (pre), or
+// straight from the partials where there are at most kChunks blocks (direct)
+template <class K, class... Args>
+void launch_fin_rows(laph_ctx *c, K pre, K direct, int R, int nrow, const double *part, int nblk, double *part_pre,
+                     Scal *sc, Args... args)
+{
+    if (nblk <= kChunks) {
+        launch_fin(c, direct, R, part, nblk, R, sc, args...);
+        return;
+    }
+    hipLaunchKernelGGL(k_prereduce, dim3(kChunks), dim3(kBS), 0, c->stream, part, nblk, nrow, part_pre);
+    launch_fin(c, pre, R, (const double *)part_pre, kChunks, R, sc, args...);
 }
 
 void read_scal(laph_ctx *c, const Scal *d, std::vector<Scal> &h)
@@ -1407,7 +1468,10 @@ void true_eo_residual(Work &w, const Op64 &hi, Vec bhat, Vec xhi, Vec tmp, Vec r
 // p = r + beta (p - omega v).  The steps alpha p + omega s are owed to the FP32 increment
 // in a ring of K (p, s) pairs and taken K at a time; FP64 reliable updates (quorum rule of
 // the CG loop) fold them with the increment into x_hi and replace r by the FP64 residual.
-// Decisions read the previous iteration's scalars, as in the CG loop.
+// Decisions read the previous iteration's scalars, as in the CG loop.  The launches go to
+// the stream one by one: replayed from a HIP graph per ring position they had no gaps inside
+// an iteration but 4-8 us at either end of it, and 8 graphs to build per solve (a solve of 20
+// sources on 8^3 x 16 6.47 ms, with graphs 7.08 ms; 16^3 x 32 160.7 / 161.0 ms).
 template <class SP, class GP, class CP, class XP>
 void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, Vec rhi, Vec tmp64,
                     int maxiter, int reliable_every, std::vector<Scal> &hs)
@@ -1452,62 +1516,25 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         d.n = cnt;
         return d;
     };
-    auto body = [&](const Op<SP, GP, CP> &op, int b) {
-        op.mhat_dot(pb[b], v, r0, part_hop);
-        hipLaunchKernelGGL(k_prereduce, dim3(kChunks), dim3(kBS), 0, c->stream, (const double *)part_hop, nblk_hop,
-                           3 * w.R, part_pre);
-        launch_fin(c, k_fin_bs_alpha, w.R, (const double *)part_pre, kChunks, w.R, w.sc);
-        launch_el(c, k_s_update<SP>, n, r, v, sb[b], w.Vh, w.R, (const Scal *)w.sc);
-        op.mhat_dot(sb[b], t, sb[b], part_hop);
-        hipLaunchKernelGGL(k_prereduce, dim3(kChunks), dim3(kBS), 0, c->stream, (const double *)part_hop, nblk_hop,
-                           3 * w.R, part_pre);
-        launch_fin(c, k_fin_bs_omega, w.R, (const double *)part_pre, kChunks, w.R, w.sc);
-        launch_el(c, k_bs_r<SP>, n, sb[b], t, r, r0, w.Vh, w.R, part_hop, (const Scal *)w.sc);
-        hipLaunchKernelGGL(k_prereduce, dim3(kChunks), dim3(kBS), 0, c->stream, (const double *)part_hop, nblk_el,
-                           3 * w.R, part_pre);
-        launch_fin(c, k_fin_bs_beta, w.R, (const double *)part_pre, kChunks, w.R, w.sc);
-    };
     Scal *pin = pinned_scal(c, w.R);
     int slot = 0;
     bool prev_ok = false;
-    hipGraphExec_t gexecs[kMaxDirs] = {};  // the body captured for each ring position
-    const bool graph_ok = w.use_graph && !c->timing;
-    if (graph_ok && !c->cap_stream) LAPH_HIP(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-    struct GraphGuard {
-        hipGraphExec_t *g;
-        ~GraphGuard()
-        {
-            for (int k = 0; k < kMaxDirs; k++)
-                if (g[k]) (void)hipGraphExecDestroy(g[k]);
-        }
-    } guard{gexecs};
+    auto body = [&](int b) {
+        lo.mhat_dot(pb[b], v, r0, part_hop);
+        launch_fin_rows(c, k_fin_bs_alpha<false>, k_fin_bs_alpha<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre, w.sc);
+        launch_el(c, k_s_update<SP>, n, r, v, sb[b], w.Vh, w.R, (const Scal *)w.sc);
+        lo.mhat_dot(sb[b], t, sb[b], part_hop);
+        launch_fin_rows(c, k_fin_bs_omega<false>, k_fin_bs_omega<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre, w.sc);
+        launch_el(c, k_bs_r<SP>, n, sb[b], t, r, r0, w.Vh, w.R, part_hop, (const Scal *)w.sc);
+        launch_fin_rows(c, k_fin_bs_beta<false>, k_fin_bs_beta<true>, w.R, 3 * w.R, part_hop, nblk_el, part_pre, w.sc,
+                        pin + (size_t)slot * w.R);
+    };
     const double kDelta2 = w.delta2;
     int since = 0;
     int why[4] = {0, 0, 0, 0};  // reliable updates by trigger: all converged, deep drop, quorum, count
     for (int it = 0; it < maxiter; it++) {
-        hipGraphExec_t &gexec = gexecs[cur];
-        if (gexec) {
-            LAPH_HIP(hipGraphLaunch(gexec, c->stream));
-        } else if (graph_ok) {
-            hipStream_t main = c->stream;
-            Op<SP, GP, CP> cap = lo;
-            cap.st = c->cap_stream;
-            c->stream = c->cap_stream;
-            hipGraph_t g = nullptr;
-            hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed);
-            if (e == hipSuccess) {
-                body(cap, cur);
-                e = hipStreamEndCapture(c->cap_stream, &g);
-            }
-            c->stream = main;
-            LAPH_HIP(e);
-            e = hipGraphInstantiate(&gexec, g, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(g);
-            LAPH_HIP(e);
-            LAPH_HIP(hipGraphLaunch(gexec, c->stream));
-        } else {
-            body(lo, cur);
-        }
+        body(cur);
+        LAPH_HIP(hipEventRecord(c->pin_ev[slot], c->stream));
         // the direction update writes the next pair's p; with every pair owed it first
         // takes all K steps (the oldest pair is the one overwritten)
         const bool take = nowed + 1 == K;
@@ -1517,9 +1544,6 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         cur = nxt;
         nowed = take ? 0 : nowed + 1;
         since++;
-        LAPH_HIP(hipMemcpyAsync(pin + (size_t)slot * w.R, w.sc, sizeof(Scal) * w.R, hipMemcpyDeviceToHost,
-                                c->stream));
-        LAPH_HIP(hipEventRecord(c->pin_ev[slot], c->stream));
         const int use = prev_ok ? slot ^ 1 : slot;
         LAPH_HIP(hipEventSynchronize(c->pin_ev[use]));
         std::copy(pin + (size_t)use * w.R, pin + (size_t)use * w.R + w.R, hs.begin());
@@ -1713,8 +1737,7 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
     // the fused body leaves the steps x += alpha p to the direction update; with K direction
     // buffers (a ring) each update writes the new direction into the next buffer and keeps
     // the old ones, and every K-th update takes the K owed steps at once: the FP32 increment
-    // is read and written every K-th iteration only (graph replay keeps one captured body per
-    // direction buffer)
+    // is read and written every K-th iteration only
     const int K = !fuse ? 1 : w.dirs > 0 ? w.dirs : kDefaultDirs;
     Vec pb[kMaxDirs];
     pb[0] = p;
@@ -1730,31 +1753,8 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
         d.n = cnt;
         return d;
     };
-    auto body = [&](const Op<SP, GP, CP> &op) {
-        if constexpr (!plain) {
-            // M p with |q|^2 and A^-1 gamma_5 q from its epilogue; M^dag q feeding the CG
-            // update directly (partials of the fused epilogues are block-major, pre-reduced
-            // to kChunks per RHS)
-            op.mhat_prep(p, q, to, part_hop);
-            hipLaunchKernelGGL(k_prereduce, dim3(kChunks), dim3(kBS), 0, c->stream, (const double *)part_hop,
-                               nblk_hop, w.R, part_pre);
-            launch_fin(c, k_fin_cg_alpha, w.R, (const double *)part_pre, kChunks, w.R, w.sc, 1);
-            op.mhat_dag_cg(q, to, r, (const Scal *)w.sc, part_hop);
-            hipLaunchKernelGGL(k_prereduce, dim3(kChunks), dim3(kBS), 0, c->stream, (const double *)part_hop,
-                               nblk_hop, w.R, part_pre);
-            launch_fin(c, k_fin_cg_beta, w.R, (const double *)part_pre, kChunks, w.R, w.sc, 0, 1, 1);
-        } else {
-            op.mhat(p, q);
-            launch_red(c, k_normsq<SP>, n, q, w.Vh, w.R, w.part);
-            launch_fin(c, k_fin_cg_alpha, w.R, (const double *)w.part, nblk, w.R, w.sc, 0);
-            op.mhat_dag(q, y, to);
-            launch_red(c, k_cg_update<SP, XP, true>, n, xlo, p, res, q, r, y, w.Vh, w.R, w.part, (const Scal *)w.sc);
-            launch_fin(c, k_fin_cg_beta, w.R, (const double *)w.part, nblk, w.R, w.sc, 1, 0, 0);
-            launch_el(c, k_cg_p<SP, XP>, n, p, owed_dirs(0, 1), r, xlo, w.Vh, w.R, (const Scal *)w.sc, 0, 0);
-        }
-    };
-    // lagged decisions (low precision): the scalars of iteration k are copied to a pinned
-    // slot behind its hops; the update rule at iteration k reads iteration k - 1's slot,
+    // lagged decisions (low precision): the scalars of iteration k are stored to a pinned
+    // slot by its last finalisation; the update rule at iteration k reads iteration k - 1's slot,
     // long complete, so the host never waits for the queue to drain (an update or the
     // convergence test comes one iteration later, which the rule tolerates)
     const bool lag = !plain;
@@ -1762,54 +1762,33 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
     Scal *pin = lag ? pinned_scal(c, w.R) : nullptr;
     int slot = 0;
     bool prev_ok = false;  // the other slot holds the previous iteration's scalars
-    hipGraphExec_t gexecs[kMaxDirs] = {};  // body captured with p in each buffer
-    const bool graph_ok = w.use_graph && !c->timing;
-    if (graph_ok && !c->cap_stream) LAPH_HIP(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-    struct GraphGuard {
-        hipGraphExec_t *g;
-        ~GraphGuard()
-        {
-            for (int k = 0; k < kMaxDirs; k++)
-                if (g[k]) (void)hipGraphExecDestroy(g[k]);
+    auto body = [&]() {
+        if constexpr (!plain) {
+            // M p with |q|^2 and A^-1 gamma_5 q from its epilogue; M^dag q feeding the CG
+            // update directly (partials of the fused epilogues are block-major)
+            lo.mhat_prep(p, q, to, part_hop);
+            launch_fin_rows(c, k_fin_cg_alpha<kFromPre>, k_fin_cg_alpha<kFromHop>, w.R, w.R, part_hop, nblk_hop,
+                            part_pre, w.sc);
+            lo.mhat_dag_cg(q, to, r, (const Scal *)w.sc, part_hop);
+            launch_fin_rows(c, k_fin_cg_beta<kFromPre>, k_fin_cg_beta<kFromHop>, w.R, w.R, part_hop, nblk_hop,
+                            part_pre, w.sc, 0, 1, pin + (size_t)slot * w.R);
+        } else {
+            lo.mhat(p, q);
+            launch_red(c, k_normsq<SP>, n, q, w.Vh, w.R, w.part);
+            launch_fin(c, k_fin_cg_alpha<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc);
+            lo.mhat_dag(q, y, to);
+            launch_red(c, k_cg_update<SP, XP, true>, n, xlo, p, res, q, r, y, w.Vh, w.R, w.part, (const Scal *)w.sc);
+            launch_fin(c, k_fin_cg_beta<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc, 1, 0, (Scal *)nullptr);
+            launch_el(c, k_cg_p<SP, XP>, n, p, owed_dirs(0, 1), r, xlo, w.Vh, w.R, (const Scal *)w.sc, 0, 0);
         }
-    } guard{gexecs};
+    };
     for (int it = 0; it < maxiter;) {
         int chunk = std::min(check_every, maxiter - it);
-        for (int k = 0; k < chunk; k++) {
-            hipGraphExec_t &gexec = gexecs[cur];
-            if (gexec) {
-                LAPH_HIP(hipGraphLaunch(gexec, c->stream));
-            } else if (graph_ok) {
-                // record the body once on the capture stream, then replay it
-                hipStream_t main = c->stream;
-                bool timing = c->timing;
-                Op<SP, GP, CP> cap = lo;
-                cap.st = c->cap_stream;
-                c->stream = c->cap_stream;
-                c->timing = false;
-                hipGraph_t g = nullptr;
-                hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed);
-                if (e == hipSuccess) {
-                    body(cap);
-                    e = hipStreamEndCapture(c->cap_stream, &g);
-                }
-                c->stream = main;
-                c->timing = timing;
-                LAPH_HIP(e);
-                e = hipGraphInstantiate(&gexec, g, nullptr, nullptr, 0);
-                (void)hipGraphDestroy(g);
-                LAPH_HIP(e);
-                LAPH_HIP(hipGraphLaunch(gexec, c->stream));
-            } else {
-                body(lo);
-            }
-        }
+        for (int k = 0; k < chunk; k++) body();
         it += chunk;
         since += chunk;
         step_now = fuse;
         if (lag) {
-            LAPH_HIP(hipMemcpyAsync(pin + (size_t)slot * w.R, w.sc, sizeof(Scal) * w.R, hipMemcpyDeviceToHost,
-                                    c->stream));
             LAPH_HIP(hipEventRecord(c->pin_ev[slot], c->stream));
             const int use = prev_ok ? slot ^ 1 : slot;
             LAPH_HIP(hipEventSynchronize(c->pin_ev[use]));
@@ -2291,7 +2270,6 @@ void solve_batch(laph_ctx *c, const double *eta, double *x, int R, int nreal, co
     long Vh = c->g.Vh;
     DiracCache &dc = *c->cur;
     Work w{c, Vh, R, nullptr, nullptr};
-    w.use_graph = sv->use_graph != 0;
     if (sv->reliable_delta > 0) w.delta2 = sv->reliable_delta * sv->reliable_delta;
     w.dirs = sv->dir_buffers;
     w.sc = (Scal *)ctx_named(c, "slv.scal", sizeof(Scal) * R);
