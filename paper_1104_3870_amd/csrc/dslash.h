@@ -114,8 +114,7 @@ enum {
     M_PLAIN_CG = 5,      // as M_PLAIN with out consumed by a CG update instead of stored
                          // (multi-RHS low-precision kernel only)
     M_INV_AFTER_DOT = 6  // as M_INV_AFTER, and also per-block partial sums of <y, out> and
-                         // |out|^2 for a second own-site field y (BiCGStab; multi-RHS
-                         // low-precision kernel only)
+                         // |out|^2 for a second own-site field y (BiCGStab)
 };
 
 struct DslashArgs {
@@ -137,6 +136,10 @@ struct DslashArgs {
     int g5d;        // 1: gamma_5 applied to D psi before the epilogue
     int wby, wbz;   // site walk: tiles of Ns x wby x wbz sites through all time slices (set
                     // by the launcher; 0: checkerboard order)
+    // M_INV_AFTER_DOT: partial[(k R + r) 3 + q], k < dslash_dot_parts, holds sums of Re <y_r, out_r>
+    // (q = 0), Im (q = 1) and |out_r|^2 (q = 2), <y, out> = sum conj(y) out
+    const void *dot_y;
+    double *partial;
 };
 
 // launcher (dslash.hip); SPI = storage of in/out/x
@@ -147,5 +150,8 @@ void launch_dslash(laph_ctx *c, int mode, const DslashArgs &a, hipStream_t st);
 template <class SP, class CP>
 void launch_clover_apply(laph_ctx *c, const void *clov, const void *x, const float *x_nrm, void *out,
                          float *out_nrm, long Vh, int R, int g5_in, hipStream_t st);
+
+// partial sums per right-hand side and value that an M_INV_AFTER_DOT launch writes
+int dslash_dot_parts(long Vh, int R);
 
 double dslash_bytes(long Vh, int R, int gbytes, int cbytes, int sbytes, bool has_norm, int mode, bool has_x);

@@ -254,6 +254,21 @@ __device__ __forceinline__ long walk_coords(unsigned pos, int ns, int nt, int pa
     return (long)xh + (long)nsh * (y + (long)ns * (z + (long)ns * t));
 }
 
+// q += (Re <y, v>, Im <y, v>, |v|^2) of one component
+__device__ __forceinline__ void dot_add(Cx<double> y, Cx<double> v, double (&q)[3])
+{
+    q[0] += y.re * v.re + y.im * v.im;
+    q[1] += y.re * v.im - y.im * v.re;
+    q[2] += v.re * v.re + v.im * v.im;
+}
+// sums over the lanes of a wave that hold the same right-hand side (lane mod R), in every lane
+__device__ __forceinline__ void wave_sum_rhs(double (&q)[3], int R)
+{
+    for (int off = 32; off >= R; off >>= 1)
+#pragma unroll
+        for (int k = 0; k < 3; k++) q[k] += __shfl_xor(q[k], off, 64);
+}
+
 template <class SP, class GP, class CP, int MODE, bool O32>
 __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
 {
@@ -262,7 +277,10 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
     long tid = (long)b * blockDim.x + threadIdx.x;
     const int R = P.R;
     const long Vh = P.Vh;
-    if (tid >= Vh * R) return;
+    constexpr bool kDot = MODE == M_INV_AFTER_DOT;
+    const bool valid = tid < Vh * R;
+    if (!kDot && !valid) return;
+    if (kDot && !valid) tid = Vh * R - 1;  // (lanes past the end take part in the sums, with zeros)
     // 32-bit lane arithmetic: the launcher guarantees Vh R < 2^28
     const unsigned pos = (unsigned)tid / (unsigned)R;
     const int r = (int)((unsigned)tid - pos * (unsigned)R);
@@ -310,7 +328,7 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
 #pragma unroll
                 for (int c = 0; c < 3; c++) res.v[a][c] = res.v[a][c] + ca * xv.v[a][c];
         }
-    } else if constexpr (MODE == M_INV_AFTER) {
+    } else if constexpr (MODE == M_INV_AFTER || kDot) {
         Spin<A> m;
         clover_mul<CP, A, O32>(cl, Vh, i, acc, m);
 #pragma unroll
@@ -342,7 +360,30 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
 #pragma unroll
             for (int c = 0; c < 3; c++) res.v[a][c] = m.v[a][c] + cc * acc.v[a][c];
     }
-    store_spinor<SP, O32>((typename SP::E *)P.out, P.out_nrm, Vh, R, i, r, res);
+    if (valid) store_spinor<SP, O32>((typename SP::E *)P.out, P.out_nrm, Vh, R, i, r, res);
+    if constexpr (kDot) {
+        __shared__ double red[256 / 64][32][3];
+        double q[3] = {0.0, 0.0, 0.0};
+        if (valid) {
+            Spin<A> y;
+            load_spinor<SP, O32>((const typename SP::E *)P.dot_y, nullptr, Vh, R, i, r, y);
+#pragma unroll
+            for (int a = 0; a < 4; a++)
+#pragma unroll
+                for (int c = 0; c < 3; c++) dot_add(y.v[a][c], res.v[a][c], q);
+        }
+        wave_sum_rhs(q, R);
+        const int lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+        if (lane < R)
+#pragma unroll
+            for (int k = 0; k < 3; k++) red[wave][lane][k] = q[k];
+        __syncthreads();
+        if ((int)threadIdx.x < R)
+#pragma unroll
+            for (int k = 0; k < 3; k++)
+                P.partial[((long)blockIdx.x * R + threadIdx.x) * 3 + k] =
+                    red[0][threadIdx.x][k] + red[1][threadIdx.x][k] + red[2][threadIdx.x][k] + red[3][threadIdx.x][k];
+    }
 }
 
 // The FP64 hop of launches with few (site, right-hand side) pairs: the rolled kernel above
@@ -375,7 +416,8 @@ __global__ __launch_bounds__(8 * kSplit) void k_dslash_split(const DslashArgs P)
             ex[d][3 + c][l] = make_double2(o1[c].re, o1[c].im);
         }
     });
-    constexpr bool kClov = MODE != M_PLAIN;
+    constexpr bool kClov = MODE != M_PLAIN, kDot = MODE == M_INV_AFTER_DOT;
+    constexpr bool kInvAfter = MODE == M_INV_AFTER || kDot;
     double cl[36];
     if (d < 2) {
         if constexpr (kClov) {
@@ -384,14 +426,18 @@ __global__ __launch_bounds__(8 * kSplit) void k_dslash_split(const DslashArgs P)
         }
     }
     __syncthreads();
-    if (d >= 2 || !valid) return;
-    Cx<double> acc[6], xv[6];
+    if (d >= 2 || (!kDot && !valid)) return;
+    Cx<double> acc[6], xv[6], yv[6];
 #pragma unroll
     for (int k = 0; k < 6; k++) {
         acc[k] = xv[k] = {0.0, 0.0};
         if (P.x) {
             const double2 e = elem<O32>((const double2 *)P.x + (long)(d * 6 + k) * Vh * R, i * R + r);
             xv[k] = {e.x, e.y};
+        }
+        if constexpr (kDot) {
+            const double2 e = elem<O32>((const double2 *)P.dot_y + (long)(d * 6 + k) * Vh * R, i * R + r);
+            yv[k] = {e.x, e.y};
         }
     }
 #pragma unroll
@@ -429,12 +475,12 @@ __global__ __launch_bounds__(8 * kSplit) void k_dslash_split(const DslashArgs P)
     };
     const double ca = P.a, cc = P.c;
     Cx<double> res[6];
-    if constexpr (MODE == M_PLAIN || MODE == M_INV_AFTER) {
+    if constexpr (MODE == M_PLAIN || kInvAfter) {
         Cx<double> m[6];
-        if constexpr (MODE == M_INV_AFTER) herm(acc, m);
+        if constexpr (kInvAfter) herm(acc, m);
 #pragma unroll
         for (int k = 0; k < 6; k++) {
-            res[k] = cc * (MODE == M_INV_AFTER ? m[k] : acc[k]);
+            res[k] = cc * (kInvAfter ? m[k] : acc[k]);
             if (P.x) res[k] = res[k] + ca * xv[k];
         }
     } else if constexpr (MODE == M_INV_OF_SUM) {
@@ -447,9 +493,22 @@ __global__ __launch_bounds__(8 * kSplit) void k_dslash_split(const DslashArgs P)
 #pragma unroll
         for (int k = 0; k < 6; k++) res[k] = res[k] + cc * acc[k];
     }
+    if (valid) {
 #pragma unroll
-    for (int k = 0; k < 6; k++)
-        elem<O32>((double2 *)P.out + (long)(d * 6 + k) * Vh * R, i * R + r) = make_double2(res[k].re, res[k].im);
+        for (int k = 0; k < 6; k++)
+            elem<O32>((double2 *)P.out + (long)(d * 6 + k) * Vh * R, i * R + r) = make_double2(res[k].re, res[k].im);
+    }
+    if constexpr (kDot) {  // each of the two waves writes its sums
+        double q[3] = {0.0, 0.0, 0.0};
+        if (valid) {
+#pragma unroll
+            for (int k = 0; k < 6; k++) dot_add(yv[k], res[k], q);
+        }
+        wave_sum_rhs(q, R);
+        if (l < R)
+#pragma unroll
+            for (int k = 0; k < 3; k++) P.partial[((2l * blockIdx.x + d) * R + l) * 3 + k] = q[k];
+    }
 }
 
 template <class SP, class CP>
@@ -495,6 +554,7 @@ void launch_modes(int mode, dim3 grid, dim3 block, hipStream_t st, const DslashA
     case M_PLAIN: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_PLAIN, O32>), grid, block, 0, st, a); break;
     case M_INV_AFTER: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER, O32>), grid, block, 0, st, a); break;
     case M_INV_OF_SUM: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_OF_SUM, O32>), grid, block, 0, st, a); break;
+    case M_INV_AFTER_DOT: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER_DOT, O32>), grid, block, 0, st, a); break;
     default: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_CLOV_ADD, O32>), grid, block, 0, st, a); break;
     }
 }
@@ -512,8 +572,15 @@ void launch_split(int mode, long n, hipStream_t st, const DslashArgs &a)
     case M_PLAIN: hipLaunchKernelGGL((k_dslash_split<M_PLAIN, O32>), grid, block, 0, st, a); break;
     case M_INV_AFTER: hipLaunchKernelGGL((k_dslash_split<M_INV_AFTER, O32>), grid, block, 0, st, a); break;
     case M_INV_OF_SUM: hipLaunchKernelGGL((k_dslash_split<M_INV_OF_SUM, O32>), grid, block, 0, st, a); break;
+    case M_INV_AFTER_DOT: hipLaunchKernelGGL((k_dslash_split<M_INV_AFTER_DOT, O32>), grid, block, 0, st, a); break;
     default: hipLaunchKernelGGL((k_dslash_split<M_CLOV_ADD, O32>), grid, block, 0, st, a); break;
     }
+}
+
+int dslash_dot_parts(long Vh, int R)
+{
+    const long n = Vh * R;
+    return n <= kSplitMost ? 2 * (int)nblocks_for(n, kSplit) : (int)nblocks_for(n, 256);
 }
 
 template <class SP, class GP, class CP>

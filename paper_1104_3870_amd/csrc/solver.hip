@@ -368,6 +368,157 @@ __global__ __launch_bounds__(kBS) void k_p_update(Vec p, Vec r, Vec v, long Vh, 
     st_site<SP>(p, Vh, R, i, rr, pv);
 }
 
+// ------------------------------------------------ FP64 BiCGStab, few partial sums
+// Where a launch of the FP64 iteration writes few partial sums, five of its twelve launches
+// are inner products and one-block finalisations that take microseconds while the chip waits.
+// Here the hops sum <r0, v> and <s, t>, |t|^2 in their epilogues, and each vector pass takes
+// all partials of the previous one itself, in every block, while its own operands are on
+// their way: seven launches.  Every block finds the same scalars; block 0 stores them.  A
+// block may then see active already cleared by block 0, which is what it would itself
+// conclude from the sums; rho is read from one of two places and stored to the other.
+// An iteration with one right-hand side: 4^3 x 8 62 -> 50 us, 16^3 x 32 192 -> 176 us.
+constexpr int kMergeMost = 1280;  // partial sums of a hop and of a vector pass, all right-hand sides
+
+// sums of ent partials [ent][3], ent a multiple of R with the right-hand side fastest, in every lane
+// for right-hand side threadIdx.x mod R
+__device__ __forceinline__ void block_sums(const double *partial, int ent, int R, double (&v)[3])
+{
+    __shared__ double lds[kBS / 64][32][3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) v[k] = 0;
+    for (int f = threadIdx.x; f < ent; f += kBS)
+#pragma unroll
+        for (int k = 0; k < 3; k++) v[k] += partial[(long)f * 3 + k];
+    for (int off = 32; off >= R; off >>= 1)
+#pragma unroll
+        for (int k = 0; k < 3; k++) v[k] += __shfl_xor(v[k], off, 64);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane < R)
+#pragma unroll
+        for (int k = 0; k < 3; k++) lds[wave][lane][k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        v[k] = 0;
+        for (int w = 0; w < kBS / 64; w++) v[k] += lds[w][threadIdx.x & (R - 1)][k];
+    }
+}
+
+// alpha = rho / <r0, v>; s = r - alpha v
+__global__ __launch_bounds__(kBS) void k_merged_s(Vec r, Vec v, Vec s, long Vh, int R, const double *part, int ent,
+                                                  Scal *sc, int odd)
+{
+    const long n = Vh * R, tid = blockIdx.x * (long)kBS + threadIdx.x;
+    const int rr = (int)(threadIdx.x & (R - 1));
+    const long i = min(tid, n - 1) / R;
+    Cx<double> a[12], b[12];
+    ld_site<S64>(r, Vh, R, i, rr, a);
+    ld_site<S64>(v, Vh, R, i, rr, b);
+    double q[3];
+    block_sums(part, ent, R, q);
+    Scal &S = sc[rr];
+    const bool act = S.active;
+    const double2 rho = odd ? S.aux : S.rho, den = make_double2(q[0], q[1]);
+    const bool bad = cnorm2(den) == 0.0 || !std::isfinite(den.x) || !std::isfinite(den.y);
+    const double2 alpha = act && !bad ? cdiv(rho, den) : make_double2(0, 0);
+    if (tid < R) {
+        S.alpha = alpha;
+        if (act && bad) {
+            S.breakdown = 1;
+            S.active = 0;
+        }
+    }
+    if (tid >= n || !act || bad) return;
+    const Cx<double> al = cx(alpha);
+#pragma unroll
+    for (int k = 0; k < 12; k++) a[k] = a[k] - al * b[k];
+    st_site<S64>(s, Vh, R, i, rr, a);
+}
+
+// omega = <t, s> / |t|^2 (the partials hold <s, t>); x += alpha p + omega s; r = s - omega t;
+// partial <r0, r>, |r|^2
+__global__ __launch_bounds__(kBS) void k_merged_xr(Vec x, Vec p, Vec s, Vec t, Vec r, Vec r0, long Vh, int R,
+                                                   const double *part, int ent, double *partial, Scal *sc)
+{
+    const long n = Vh * R, tid = blockIdx.x * (long)kBS + threadIdx.x;
+    const int rr = (int)(threadIdx.x & (R - 1));
+    const long i = min(tid, n - 1) / R;
+    Cx<double> xv[12], pv[12], sv[12], tv[12];
+    ld_site<S64>(s, Vh, R, i, rr, sv);
+    ld_site<S64>(t, Vh, R, i, rr, tv);
+    ld_site<S64>(x, Vh, R, i, rr, xv);
+    ld_site<S64>(p, Vh, R, i, rr, pv);
+    double q[3];
+    block_sums(part, ent, R, q);
+    Scal &S = sc[rr];
+    const bool act = S.active;
+    const bool bad = !(q[2] > 0.0) || !std::isfinite(q[2]);
+    const double2 omega = act && !bad ? make_double2(q[0] / q[2], -q[1] / q[2]) : make_double2(0, 0);
+    const Cx<double> al = cx(S.alpha), om = cx(omega);
+    if (tid < R) {
+        S.omega = omega;
+        if (act && bad) {
+            S.breakdown = 1;
+            S.active = 0;
+        }
+    }
+    double acc[3] = {0, 0, 0};
+    if (tid < n && act && !bad) {
+        Cx<double> z[12];
+        ld_site<S64>(r0, Vh, R, i, rr, z);
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            xv[k] = xv[k] + al * pv[k] + om * sv[k];
+            sv[k] = sv[k] - om * tv[k];
+        }
+        st_site<S64>(x, Vh, R, i, rr, xv);
+        st_site<S64>(r, Vh, R, i, rr, sv);
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            acc[0] += z[k].re * sv[k].re + z[k].im * sv[k].im;
+            acc[1] += z[k].re * sv[k].im - z[k].im * sv[k].re;
+            acc[2] += sv[k].re * sv[k].re + sv[k].im * sv[k].im;
+        }
+    }
+    block_partial<3>(acc, R, partial);
+}
+
+// rho_new = <r0, r>, beta = (rho_new / rho)(alpha / omega), |r|^2, convergence; p = r + beta (p - omega v)
+__global__ __launch_bounds__(kBS) void k_merged_p(Vec p, Vec r, Vec v, long Vh, int R, const double *part, int ent,
+                                                  Scal *sc, int odd)
+{
+    const long n = Vh * R, tid = blockIdx.x * (long)kBS + threadIdx.x;
+    const int rr = (int)(threadIdx.x & (R - 1));
+    const long i = min(tid, n - 1) / R;
+    Cx<double> pv[12], rv[12], vv[12];
+    ld_site<S64>(p, Vh, R, i, rr, pv);
+    ld_site<S64>(r, Vh, R, i, rr, rv);
+    ld_site<S64>(v, Vh, R, i, rr, vv);
+    double q[3];
+    block_sums(part, ent, R, q);
+    Scal &S = sc[rr];
+    const bool act = S.active;
+    const double2 rho = odd ? S.aux : S.rho, rn = make_double2(q[0], q[1]);
+    const bool bad = !std::isfinite(q[2]) || cnorm2(rho) == 0.0 || cnorm2(S.omega) == 0.0;
+    const bool done = q[2] <= S.tol2;
+    const double2 beta = act && !bad ? cmul(cdiv(rn, rho), cdiv(S.alpha, S.omega)) : make_double2(0, 0);
+    const Cx<double> be = cx(beta), om = cx(S.omega);
+    if (tid < R) {
+        S.beta = beta;
+        if (act) {
+            S.iters += 1;
+            S.r2 = q[2];
+            (odd ? S.rho : S.aux) = rn;
+            if (bad) S.breakdown = 1;
+            if (bad || done) S.active = 0;
+        }
+    }
+    if (tid >= n || !act || bad || done) return;
+#pragma unroll
+    for (int k = 0; k < 12; k++) pv[k] = rv[k] + be * (pv[k] - om * vv[k]);
+    st_site<S64>(p, Vh, R, i, rr, pv);
+}
+
 // ------------------------------------------------------------ FP64 / reliable updates
 // xhi += xlo; xlo = 0 (right-hand sides with mask set, or all when all_rhs)
 template <class XP>
@@ -1307,7 +1458,7 @@ struct Op {
         dslash_ext(M_INV_AFTER_DAG, 1, te, out, &in, 1.0, -1.0, 0, &to, partial);
     }
     // mhat with per-block partials of <y, out> and |out|^2 from the second hop's epilogue
-    // (low precision, LDS-staged kernel; partials [block][value][RHS], see MrArgs)
+    // (partials [block][value][RHS], see MrArgs; FP64: [block][RHS][value], see DslashArgs)
     void mhat_dot(Vec in, Vec out, Vec y, double *partial) const
     {
         dslash(M_INV_AFTER, 0, in, te, nullptr, 0.0, 1.0, 0);
@@ -1318,7 +1469,16 @@ struct Op {
             m.partial = partial;
             launch_dslash_mr<SP>(c, M_INV_AFTER_DOT, m, st);
         } else {
-            laph_fail(LAPH_EINVAL, "fused BiCGStab products are low precision only");
+            DslashArgs a = base(1);
+            a.in = te.d;
+            a.out = out.d;
+            a.x = in.d;
+            a.clov = cinv(1);
+            a.a = 1.0;
+            a.c = -1.0;
+            a.dot_y = y.d;
+            a.partial = partial;
+            launch_dslash<SP, GP, CP>(c, M_INV_AFTER_DOT, a, st);
         }
     }
 };
@@ -1624,9 +1784,24 @@ void bicgstab_plain(Work &w, const Op<S64, GP, CP> &op, Vec xhi, Vec rhi, int ma
     read_scal(c, w.sc, hs);
     std::vector<double> r2_min(w.R);
     for (int q = 0; q < w.R; q++) r2_min[q] = hs[q].r2;
+    // the hop's partials and, behind them, those of the update of x and r
+    const int ent_hop = dslash_dot_parts(w.Vh, w.R) * w.R, ent_xr = (int)nblocks_for(n, kBS) * w.R;
+    const bool merged = ent_hop + ent_xr <= kMergeMost;
+    static_assert(3 * kMergeMost <= 4 * kMaxBlocks, "both fit w.part");
+    double *part_xr = w.part + 3 * ent_hop;
     for (int it = 0; it < maxiter;) {
         int chunk = std::min(check_every, maxiter - it);
         for (int k = 0; k < chunk; k++) {
+            if (merged) {
+                const int odd = (it + k) & 1;
+                op.mhat_dot(p, v, r0, w.part);
+                launch_el(c, k_merged_s, n, r, v, s, w.Vh, w.R, (const double *)w.part, ent_hop, w.sc, odd);
+                op.mhat_dot(s, t, s, w.part);
+                launch_el(c, k_merged_xr, n, xlo, p, s, t, r, r0, w.Vh, w.R, (const double *)w.part, ent_hop, part_xr,
+                          w.sc);
+                launch_el(c, k_merged_p, n, p, r, v, w.Vh, w.R, (const double *)part_xr, ent_xr, w.sc, odd);
+                continue;
+            }
             op.mhat(p, v);
             launch_red(c, k_dot<SP>, n, r0, v, w.Vh, w.R, w.part);
             launch_fin(c, k_fin_alpha, w.R, (const double *)w.part, nblk, w.R, w.sc);

@@ -1,6 +1,7 @@
-"""Low-precision solves at the edges of their reductions: from less than one block of partial
-sums to 1024 blocks (taken in one stage) and past them (two stages), with block sizes from 1
-to 32 right-hand sides, judged by the true residual of the FP64 operator.
+"""Solves at the edges of their reductions, judged by the true residual of the FP64 operator.
+Low precision: from less than one block of partial sums to 1024 blocks (taken in one stage) and
+past them (two stages).  FP64 BiCGStab: partial sums taken by the vector passes themselves, from
+the split and from the rolled hop, with ragged last blocks, up to and past their largest number.
 
 Bound: the solver stops on its own FP64 residual of 1e-10, so an independent evaluation can
 exceed it by that evaluation's rounding only; twice the target covers it."""
@@ -12,9 +13,12 @@ from gpu_util import dev, say
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("solver", ["bicgstab", "cgnr"])
-@pytest.mark.parametrize("ns,nt,R,prec", [(4, 4, 1, "f16"), (4, 2, 32, "f32"), (6, 4, 4, "bf16"),
-                                          (16, 4, 32, "f16"), (16, 6, 32, "f16")])
+LOW = [(4, 4, 1, "f16"), (4, 2, 32, "f32"), (6, 4, 4, "bf16"), (16, 4, 32, "f16"), (16, 6, 32, "f16")]
+FP64 = [(4, 2, 1, "f64"), (4, 2, 16, "f64"), (4, 2, 32, "f64"), (6, 10, 1, "f64"), (6, 10, 4, "f64"),
+        (16, 16, 1, "f64"), (16, 18, 1, "f64"), (12, 20, 2, "f64")]
+
+
+@pytest.mark.parametrize("ns,nt,R,prec,solver", [(*c, "bicgstab") for c in LOW + FP64] + [(*c, "cgnr") for c in LOW])
 def test_solve_reduction_edges(ns, nt, R, prec, solver):
     import torch
 
