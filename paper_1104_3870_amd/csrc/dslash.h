@@ -117,6 +117,21 @@ enum {
                          // |out|^2 for a second own-site field y (BiCGStab)
 };
 
+// m = ceil(2^32 / d): umulhi(n, m) = floor(n / d) whenever n d < 2^32 (m d - 2^32 < d);
+// 0 for d = 1
+inline unsigned umulhi_magic(long d)
+{
+    if (d <= 1) return 0;
+    return (unsigned)(((1ull << 32) + (unsigned long long)d - 1) / (unsigned long long)d);
+}
+// n / d through the launcher's multiply-high reciprocal m; m = 0 stands for d = 1 (the
+// launcher guarantees a valid m for every other divisor, so no division code is emitted)
+__device__ __forceinline__ unsigned udiv(unsigned n, unsigned d, unsigned m)
+{
+    (void)d;
+    return m ? __umulhi(n, m) : n;
+}
+
 struct DslashArgs {
     void *out;
     const void *in;
@@ -140,6 +155,7 @@ struct DslashArgs {
     // (q = 0), Im (q = 1) and |out_r|^2 (q = 2), <y, out> = sum conj(y) out
     const void *dot_y;
     double *partial;
+    unsigned m_R, m_nsh, m_ns;  // reciprocals of R, ns/2 and ns for udiv (split kernel)
 };
 
 // launcher (dslash.hip); SPI = storage of in/out/x

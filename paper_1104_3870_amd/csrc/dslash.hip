@@ -181,11 +181,12 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &P, int d, long i, int 
     const int st = fwd ? 1 : -1;
     int xx = x, yy = y, zz = z, tt = t;
     double w = mu == 3 ? P.wt : P.ws;
-    if (mu == 0) xx = (x + st + ns) % ns;
-    if (mu == 1) yy = (y + st + ns) % ns;
-    if (mu == 2) zz = (z + st + ns) % ns;
+    auto wrap = [](int a, int m) { return a < 0 ? a + m : a >= m ? a - m : a; };
+    if (mu == 0) xx = wrap(x + st, ns);
+    if (mu == 1) yy = wrap(y + st, ns);
+    if (mu == 2) zz = wrap(z + st, ns);
     if (mu == 3) {
-        tt = (t + st + nt) % nt;
+        tt = wrap(t + st, nt);
         if (fwd ? t + 1 == nt : t == 0) w *= P.bct;
     }
     const long nb = lex_index(xx, yy, zz, tt, ns) >> 1;
@@ -388,126 +389,129 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
 
 // The FP64 hop of launches with few (site, right-hand side) pairs: the rolled kernel above
 // walks eight directions one memory latency after the other, which is what bounds it while
-// the chip is not full (12 us for the 256 sites of one parity of 4^3 x 8, 5 us here).  Here a workgroup
-// takes 64 pairs with one wave per direction, so all eight neighbours are read at once; the
-// products go through LDS, and waves 0 and 1 add them up in direction order and apply the
-// clover epilogue to one chirality each (their clover block is loaded ahead of the barrier).
+// the chip is not full.  Here a workgroup takes 64 pairs with one wave per direction, so all
+// eight neighbours are read at once; the products go through LDS, and twelve waves, one per
+// spin-colour component, add them up in direction order and multiply by their row of the
+// clover block, whose elements they loaded at the start.  256 sites of one parity of 4^3 x 8
+// (between events): 15.6 us rolled, 9.2 us with two waves for the sums, one per chirality, and
+// general integer divisions ahead of the first load, 7.9 us here.
 constexpr int kSplit = 64;
 
-template <int MODE, bool O32>
-__global__ __launch_bounds__(8 * kSplit) void k_dslash_split(const DslashArgs P)
+// (br + i bi) z with one of the two zero and the other +-1, known at compile time
+__device__ __forceinline__ Cx<double> unit_of(double br, double bi, Cx<double> z)
 {
-    __shared__ double2 ex[8][6][kSplit];
-    const int d = __builtin_amdgcn_readfirstlane(threadIdx.x / kSplit), l = threadIdx.x & (kSplit - 1);
-    const int R = P.R;
-    const long Vh = P.Vh;
-    const long tid = (long)xcd_block(blockIdx.x, gridDim.x) * kSplit + l;
-    const bool valid = tid < Vh * R;
-    const unsigned pos = (unsigned)tid / (unsigned)R;
-    const long i = valid ? pos : 0;
-    const int r = valid ? (int)((unsigned)tid - pos * (unsigned)R) : 0;
-    int x, y, z, t;
-    cb_coords(i, P.par, P.ns, x, y, z, t);
-    hop_dir<O32>(P, d, i, r, x, y, z, t,
-                 [&](const Cx<double> (&o0)[3], const Cx<double> (&o1)[3], const HopCoef &, double, bool) {
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            ex[d][c][l] = make_double2(o0[c].re, o0[c].im);
-            ex[d][3 + c][l] = make_double2(o1[c].re, o1[c].im);
-        }
-    });
-    constexpr bool kClov = MODE != M_PLAIN, kDot = MODE == M_INV_AFTER_DOT;
-    constexpr bool kInvAfter = MODE == M_INV_AFTER || kDot;
-    double cl[36];
-    if (d < 2) {
-        if constexpr (kClov) {
-#pragma unroll
-            for (int k = 0; k < 36; k++) cl[k] = elem<O32>((const double *)P.clov + (long)(d * 36 + k) * Vh, i);
-        }
-    }
-    __syncthreads();
-    if (d >= 2 || (!kDot && !valid)) return;
-    Cx<double> acc[6], xv[6], yv[6];
-#pragma unroll
-    for (int k = 0; k < 6; k++) {
-        acc[k] = xv[k] = {0.0, 0.0};
-        if (P.x) {
-            const double2 e = elem<O32>((const double2 *)P.x + (long)(d * 6 + k) * Vh * R, i * R + r);
-            xv[k] = {e.x, e.y};
-        }
-        if constexpr (kDot) {
-            const double2 e = elem<O32>((const double2 *)P.dot_y + (long)(d * 6 + k) * Vh * R, i * R + r);
-            yv[k] = {e.x, e.y};
-        }
-    }
+    return br != 0.0 ? Cx<double>{br * z.re, br * z.im} : Cx<double>{-bi * z.im, bi * z.re};
+}
+
+// component c of spin S of the sum over directions, from ex[direction][colour vector][pair]
+template <int S>
+__device__ __forceinline__ Cx<double> split_sum(const double2 (&ex)[8][6][kSplit], int c, int l)
+{
+    constexpr HopCoef kc[4] = {hop_coef(0), hop_coef(1), hop_coef(2), hop_coef(3)};
+    Cx<double> acc = {0.0, 0.0};
 #pragma unroll
     for (int e = 0; e < 8; e++) {
-        constexpr HopCoef kc[4] = {hop_coef(0), hop_coef(1), hop_coef(2), hop_coef(3)};
         const HopCoef &q = kc[e >> 1];
         const double sb = (e & 1) ? -1.0 : 1.0;
-        // wave 0 adds o0 and o1, wave 1 what the lower components take of them
-        const int f = d && e < 4 ? 3 : 0;
+        const bool second = S == 1 || (S == 2 ? e < 4 : S == 3 && e >= 4);  // o1 or o0
+        const double2 a = ex[e][(second ? 3 : 0) + c][l];
+        const Cx<double> u = {a.x, a.y};
+        acc = acc + (S < 2 ? u : unit_of(sb * (S == 2 ? q.b2r : q.b3r), sb * (S == 2 ? q.b2i : q.b3i), u));
+    }
+    return acc;
+}
+
+template <int MODE>
+__global__ __launch_bounds__(12 * kSplit) void k_dslash_split(const DslashArgs P)
+{
+    __shared__ double2 ex[8][6][kSplit], mid[12][kSplit];
+    constexpr bool kClov = MODE != M_PLAIN, kDot = MODE == M_INV_AFTER_DOT;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kSplit), l = threadIdx.x & (kSplit - 1);
+    const unsigned n = (unsigned)(P.Vh * P.R), R = P.R, ns = P.ns;
+    const unsigned tid = xcd_block(blockIdx.x, gridDim.x) * kSplit + l;
+    const bool valid = tid < n;
+    // (lanes past the end read site 0 and store nothing)
+    const unsigned i = valid ? udiv(tid, R, P.m_R) : 0, r = valid ? tid - i * R : 0;
+    const unsigned row = udiv(i, ns / 2, P.m_nsh), row2 = udiv(row, ns, P.m_ns), t = udiv(row2, ns, P.m_ns);
+    const int y = row - row2 * ns, z = row2 - t * ns;
+    const int x = 2 * (int)(i - row * (ns / 2)) + ((y + z + (int)t + P.par) & 1);
+    // this wave's component, its clover row and its operands
+    const int s = w / 3, ch = w / 6, k = w % 6;
+    double cd = 0.0, cl[5][2];
+    if constexpr (kClov) {
+        const double *C = (const double *)P.clov + (long)(ch * 36) * P.Vh;
+        cd = elem<true>(C + (long)k * P.Vh, i);
 #pragma unroll
-        for (int c = 0; c < 3; c++) {
-            const double2 a = ex[e][f + c][l], b = ex[e][3 - f + c][l];
-            const Cx<double> u = {a.x, a.y}, v = {b.x, b.y};
-            acc[c] = acc[c] + (d ? unit_mul(sb * q.b2r, sb * q.b2i, u) : u);
-            acc[3 + c] = acc[3 + c] + (d ? unit_mul(sb * q.b3r, sb * q.b3i, v) : v);
+        for (int j = 0; j < 5; j++) {
+            const int c = j < k ? j : j + 1, hi = max(k, c), lo = min(k, c), e = 6 + hi * (hi - 1) + 2 * lo;
+            cl[j][0] = elem<true>(C + (long)e * P.Vh, i);
+            cl[j][1] = elem<true>(C + (long)(e + 1) * P.Vh, i);
         }
     }
-    if (P.g5d && d) {
-#pragma unroll
-        for (int k = 0; k < 6; k++) acc[k] = cneg(acc[k]);
+    const long own = (long)w * n;  // plane of this component
+    Cx<double> xv = {0.0, 0.0}, yv = {0.0, 0.0};
+    if (P.x) {
+        const double2 e = elem<true>((const double2 *)P.x + own, i * R + r);
+        xv = {e.x, e.y};
     }
-    auto herm = [&](const Cx<double> (&v)[6], Cx<double> (&o)[6]) {
+    if constexpr (kDot) {
+        const double2 e = elem<true>((const double2 *)P.dot_y + own, i * R + r);
+        yv = {e.x, e.y};
+    }
+    if (w < 8)
+        hop_dir<true>(P, w, i, r, x, y, z, t,
+                      [&](const Cx<double> (&o0)[3], const Cx<double> (&o1)[3], const HopCoef &, double, bool) {
 #pragma unroll
-        for (int k = 0; k < 6; k++) o[k] = cl[k] * v[k];
-        int e = 6;
-#pragma unroll
-        for (int a = 1; a < 6; a++)
-#pragma unroll
-            for (int c = 0; c < a; c++) {
-                const Cx<double> L = {cl[e], cl[e + 1]};
-                e += 2;
-                o[a] = o[a] + L * v[c];
-                o[c] = o[c] + conjmul(L, v[a]);
+            for (int c = 0; c < 3; c++) {
+                ex[w][c][l] = make_double2(o0[c].re, o0[c].im);
+                ex[w][3 + c][l] = make_double2(o1[c].re, o1[c].im);
             }
-    };
+        });
+    __syncthreads();
+    const int c = w - 3 * s;
+    Cx<double> acc = s == 0 ? split_sum<0>(ex, c, l) : s == 1 ? split_sum<1>(ex, c, l)
+                   : s == 2 ? split_sum<2>(ex, c, l) : split_sum<3>(ex, c, l);
+    if (P.g5d && s >= 2) acc = cneg(acc);
     const double ca = P.a, cc = P.c;
-    Cx<double> res[6];
-    if constexpr (MODE == M_PLAIN || kInvAfter) {
-        Cx<double> m[6];
-        if constexpr (kInvAfter) herm(acc, m);
+    Cx<double> m = acc;
+    if constexpr (kClov) {
+        if constexpr (MODE == M_INV_OF_SUM) m = ca * xv + cc * acc;
+        if constexpr (MODE == M_CLOV_ADD) m = xv;
+        mid[w][l] = make_double2(m.re, m.im);
+        __syncthreads();
+        m = cd * m;
 #pragma unroll
-        for (int k = 0; k < 6; k++) {
-            res[k] = cc * (kInvAfter ? m[k] : acc[k]);
-            if (P.x) res[k] = res[k] + ca * xv[k];
+        for (int j = 0; j < 5; j++) {
+            const int o = j < k ? j : j + 1;
+            const double2 v = mid[ch * 6 + o][l];
+            m = m + Cx<double>{cl[j][0], j < k ? cl[j][1] : -cl[j][1]} * Cx<double>{v.x, v.y};
         }
-    } else if constexpr (MODE == M_INV_OF_SUM) {
-        Cx<double> sum[6];
-#pragma unroll
-        for (int k = 0; k < 6; k++) sum[k] = ca * xv[k] + cc * acc[k];
-        herm(sum, res);
-    } else {  // M_CLOV_ADD
-        herm(xv, res);
-#pragma unroll
-        for (int k = 0; k < 6; k++) res[k] = res[k] + cc * acc[k];
     }
-    if (valid) {
-#pragma unroll
-        for (int k = 0; k < 6; k++)
-            elem<O32>((double2 *)P.out + (long)(d * 6 + k) * Vh * R, i * R + r) = make_double2(res[k].re, res[k].im);
+    Cx<double> res = m;
+    if constexpr (MODE == M_CLOV_ADD) {
+        res = m + cc * acc;
+    } else if constexpr (MODE != M_INV_OF_SUM) {
+        res = cc * m;
+        if (P.x) res = res + ca * xv;
     }
-    if constexpr (kDot) {  // each of the two waves writes its sums
+    if (valid) elem<true>((double2 *)P.out + own, i * R + r) = make_double2(res.re, res.im);
+    if constexpr (kDot) {
         double q[3] = {0.0, 0.0, 0.0};
-        if (valid) {
-#pragma unroll
-            for (int k = 0; k < 6; k++) dot_add(yv[k], res[k], q);
-        }
+        if (valid) dot_add(yv, res, q);
         wave_sum_rhs(q, R);
-        if (l < R)
+        double(*red)[32][3] = (double(*)[32][3])ex;  // (every read of ex lies before the last barrier)
+        if (l < (int)R)
 #pragma unroll
-            for (int k = 0; k < 3; k++) P.partial[((2l * blockIdx.x + d) * R + l) * 3 + k] = q[k];
+            for (int e = 0; e < 3; e++) red[w][l][e] = q[e];
+        __syncthreads();
+        if (threadIdx.x < R)
+#pragma unroll
+            for (int e = 0; e < 3; e++) {
+                double sum = 0.0;
+#pragma unroll
+                for (int b = 0; b < 12; b++) sum += red[b][threadIdx.x][e];
+                P.partial[((long)blockIdx.x * R + threadIdx.x) * 3 + e] = sum;
+            }
     }
 }
 
@@ -559,28 +563,27 @@ void launch_modes(int mode, dim3 grid, dim3 block, hipStream_t st, const DslashA
     }
 }
 
-// pairs up to which the split kernel is the faster one (per launch, rolled against split):
-// 256: 11.7 / 5.0 us, 4096: 12.2 / 5.9, 13824: 14.8 / 7.7, 32768: 16.2 / 15.0; with 65536 it is
-// 3% behind, with 131072 (R = 32) 28 / 33 us
+// pairs up to which the split kernel is the faster one (between events, rolled against split):
+// 256: 15.6 / 7.9 us, 4096: 16.6 / 9.3, 13824: 19.5 / 10.9, 32768: 20.6 / 18.9; with 65536 it is
+// 2% behind, 9% with 32 right-hand sides, with 131072 (R = 32) 31.9 / 40.0 us
 constexpr long kSplitMost = 32768;
 
-template <bool O32>
 void launch_split(int mode, long n, hipStream_t st, const DslashArgs &a)
 {
-    const dim3 grid(nblocks_for(n, kSplit)), block(8 * kSplit);
+    const dim3 grid(nblocks_for(n, kSplit)), block(12 * kSplit);
     switch (mode) {
-    case M_PLAIN: hipLaunchKernelGGL((k_dslash_split<M_PLAIN, O32>), grid, block, 0, st, a); break;
-    case M_INV_AFTER: hipLaunchKernelGGL((k_dslash_split<M_INV_AFTER, O32>), grid, block, 0, st, a); break;
-    case M_INV_OF_SUM: hipLaunchKernelGGL((k_dslash_split<M_INV_OF_SUM, O32>), grid, block, 0, st, a); break;
-    case M_INV_AFTER_DOT: hipLaunchKernelGGL((k_dslash_split<M_INV_AFTER_DOT, O32>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_dslash_split<M_CLOV_ADD, O32>), grid, block, 0, st, a); break;
+    case M_PLAIN: hipLaunchKernelGGL(k_dslash_split<M_PLAIN>, grid, block, 0, st, a); break;
+    case M_INV_AFTER: hipLaunchKernelGGL(k_dslash_split<M_INV_AFTER>, grid, block, 0, st, a); break;
+    case M_INV_OF_SUM: hipLaunchKernelGGL(k_dslash_split<M_INV_OF_SUM>, grid, block, 0, st, a); break;
+    case M_INV_AFTER_DOT: hipLaunchKernelGGL(k_dslash_split<M_INV_AFTER_DOT>, grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL(k_dslash_split<M_CLOV_ADD>, grid, block, 0, st, a); break;
     }
 }
 
 int dslash_dot_parts(long Vh, int R)
 {
     const long n = Vh * R;
-    return n <= kSplitMost ? 2 * (int)nblocks_for(n, kSplit) : (int)nblocks_for(n, 256);
+    return (int)nblocks_for(n, n <= kSplitMost ? kSplit : 256);
 }
 
 template <class SP, class GP, class CP>
@@ -600,8 +603,11 @@ void launch_dslash(laph_ctx *c, int mode, const DslashArgs &a, hipStream_t st)
     DslashArgs b = a;
     b.wby = b.wbz = 0;
     if (a.R >= 8) b.wby = b.wbz = (a.ns % 3 == 0) ? 3 : 2;
+    b.m_R = umulhi_magic(a.R);  // (exact: every index is below kSplitMost)
+    b.m_nsh = umulhi_magic(a.ns / 2);
+    b.m_ns = umulhi_magic(a.ns);
     if (n <= kSplitMost)
-        launch_split<true>(mode, n, st, b);
+        launch_split(mode, n, st, b);
     else
         launch_modes<SP, GP, CP, true>(mode, grid, block, st, b);
     LAPH_HIP(hipGetLastError());

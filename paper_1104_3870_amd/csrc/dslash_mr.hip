@@ -376,14 +376,6 @@ __device__ __forceinline__ void clover_one(const float4 *p, const Cx<float> (&in
 // sites per block for R right-hand sides (block = S R lanes)
 inline size_t lds_bytes(int S) { return (size_t)S * (8 * kLkF4 + 18) * sizeof(float4); }
 
-// n / d through the launcher's multiply-high reciprocal m; m = 0 stands for d = 1 (the
-// launcher guarantees a valid m for every other divisor, so no division code is emitted)
-__device__ __forceinline__ unsigned udiv(unsigned n, unsigned d, unsigned m)
-{
-    (void)d;
-    return m ? __umulhi(n, m) : n;
-}
-
 // checkerboard index and coordinates of position pos of the site walk (MrArgs::wby):
 // tiles of ns x by x bz sites (full rows) one after the other, each visited slice by slice
 // through all nt time slices, the sites of a tile slice in (x, y, z) order.  The XCD remap
@@ -824,13 +816,6 @@ static int walk_tile(int ns, int k)
     return 0;
 }
 
-// m = ceil(2^32 / d): umulhi(n, m) = floor(n / d) whenever n d < 2^32 (m d - 2^32 < d);
-// 0 for d = 1
-static unsigned umulhi_magic(long d)
-{
-    if (d <= 1) return 0;
-    return (unsigned)(((1ull << 32) + (unsigned long long)d - 1) / (unsigned long long)d);
-}
 // every index n the kernel divides by d is below nmax: the reciprocal is exact when
 static bool magic_ok(long d, long nmax) { return (unsigned long long)nmax * (unsigned long long)d < (1ull << 32); }
 
