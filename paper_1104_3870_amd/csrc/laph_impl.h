@@ -187,11 +187,10 @@ struct laph_ctx {
     // tiled walk, tile_override > 0 fixes the sites per block
     int walk_mode = 0;
     int tile_override = 0;
-    // pinned two-slot readback of the per-RHS Krylov scalars and the events marking each
-    // slot's copy (the CG loop reads the previous iteration's slot without draining the queue)
+    // pinned host memory of the solver's scalars (slots written or read by kernels) and the
+    // events marking when a slot is complete or free again
     void *pin = nullptr;
-    size_t pin_bytes = 0;
-    hipEvent_t pin_ev[2] = {nullptr, nullptr};
+    hipEvent_t pin_ev[3] = {nullptr, nullptr, nullptr};
     // timing
     struct TimeAcc {
         double ms = 0, bytes = 0;

@@ -484,8 +484,9 @@ __global__ __launch_bounds__(kBS) void k_merged_xr(Vec x, Vec p, Vec s, Vec t, V
 }
 
 // rho_new = <r0, r>, beta = (rho_new / rho)(alpha / omega), |r|^2, convergence; p = r + beta (p - omega v)
+// (block 0 leaves a copy of the scalars in pin)
 __global__ __launch_bounds__(kBS) void k_merged_p(Vec p, Vec r, Vec v, long Vh, int R, const double *part, int ent,
-                                                  Scal *sc, int odd)
+                                                  Scal *sc, int odd, Scal *pin)
 {
     const long n = Vh * R, tid = blockIdx.x * (long)kBS + threadIdx.x;
     const int rr = (int)(threadIdx.x & (R - 1));
@@ -512,6 +513,11 @@ __global__ __launch_bounds__(kBS) void k_merged_p(Vec p, Vec r, Vec v, long Vh, 
             if (bad) S.breakdown = 1;
             if (bad || done) S.active = 0;
         }
+    }
+    if (blockIdx.x == 0) {
+        __syncthreads();
+        for (int k = threadIdx.x; k < R * (int)(sizeof(Scal) / 8); k += kBS)
+            ((double *)pin)[k] = ((const double *)sc)[k];
     }
     if (tid >= n || !act || bad || done) return;
 #pragma unroll
@@ -1536,25 +1542,44 @@ void launch_fin_rows(laph_ctx *c, K pre, K direct, int R, int nrow, const double
     launch_fin(c, pre, R, (const double *)part_pre, kChunks, R, sc, args...);
 }
 
-void read_scal(laph_ctx *c, const Scal *d, std::vector<Scal> &h)
+// Pinned slots of up to 32 right-hand sides, owned by the context: two that the iterations'
+// last kernels fill in turn, one for read_scal, one for write_scal, one for residual sums.
+// Kernels load and store them in place: a copy command, to or from pageable memory most of
+// all, keeps the stream idle for tens of microseconds on either side of it.
+enum { kPinIter, kPinRead = 2, kPinWrite, kPinSums, kPinSlots };
+constexpr int kPinRhs = 32;
+static Scal *pinned_scal(laph_ctx *c, int slot)
 {
-    LAPH_HIP(hipMemcpyAsync(h.data(), d, sizeof(Scal) * h.size(), hipMemcpyDeviceToHost, c->stream));
-    LAPH_HIP(hipStreamSynchronize(c->stream));
-}
-// pinned two-slot scalar readback for the CG loop (grown on demand, owned by the context)
-static Scal *pinned_scal(laph_ctx *c, int R)
-{
-    const size_t need = 2 * sizeof(Scal) * (size_t)R;
-    if (c->pin_bytes < need) {
-        if (c->pin) LAPH_HIP(hipHostFree(c->pin));
-        c->pin = nullptr;
-        c->pin_bytes = 0;
-        LAPH_HIP(hipHostMalloc(&c->pin, need, hipHostMallocDefault));
-        c->pin_bytes = need;
-    }
+    if (!c->pin)
+        LAPH_HIP(hipHostMalloc(&c->pin, sizeof(Scal) * kPinRhs * kPinSlots, hipHostMallocDefault));
     for (hipEvent_t &e : c->pin_ev)
         if (!e) LAPH_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    return (Scal *)c->pin;
+    return (Scal *)c->pin + (size_t)slot * kPinRhs;
+}
+
+__global__ __launch_bounds__(kBS) void k_move_scal(const double *from, double *to, int n)
+{
+    const int k = blockIdx.x * kBS + threadIdx.x;
+    if (k < n) to[k] = from[k];
+}
+
+void read_scal(laph_ctx *c, const Scal *d, std::vector<Scal> &h)
+{
+    Scal *pin = pinned_scal(c, kPinRead);
+    launch_el(c, k_move_scal, (long)(sizeof(Scal) / 8 * h.size()), (const double *)d, (double *)pin,
+              (int)(sizeof(Scal) / 8 * h.size()));
+    LAPH_HIP(hipStreamSynchronize(c->stream));
+    std::copy(pin, pin + h.size(), h.begin());
+}
+
+void write_scal(laph_ctx *c, Scal *d, const std::vector<Scal> &h)
+{
+    Scal *pin = pinned_scal(c, kPinWrite);
+    LAPH_HIP(hipEventSynchronize(c->pin_ev[2]));  // the kernel of the last write has read the slot
+    std::copy(h.begin(), h.end(), pin);
+    launch_el(c, k_move_scal, (long)(sizeof(Scal) / 8 * h.size()), (const double *)pin, (double *)d,
+              (int)(sizeof(Scal) / 8 * h.size()));
+    LAPH_HIP(hipEventRecord(c->pin_ev[2], c->stream));
 }
 
 // direction buffers of the fused CG loop where the solver parameters leave them open: the
@@ -1596,11 +1621,6 @@ struct UpdateVote {
     bool all_conv() const { return nact > 0 && nconv == nact; }
     bool want() const { return deep || all_conv() || quorum(); }
 };
-
-void write_scal(laph_ctx *c, Scal *d, const std::vector<Scal> &h)
-{
-    LAPH_HIP(hipMemcpyAsync(d, h.data(), sizeof(Scal) * h.size(), hipMemcpyHostToDevice, c->stream));
-}
 
 // rhi = bhat - Mhat xhi for masked RHS (FP64), then r2hi / masks (rlo: the residual in
 // storage precision SP instead of rhi, for the right-hand sides it is formed for)
@@ -1676,7 +1696,7 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         d.n = cnt;
         return d;
     };
-    Scal *pin = pinned_scal(c, w.R);
+    Scal *const pin = pinned_scal(c, kPinIter);
     int slot = 0;
     bool prev_ok = false;
     auto body = [&](int b) {
@@ -1687,7 +1707,7 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         launch_fin_rows(c, k_fin_bs_omega<false>, k_fin_bs_omega<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre, w.sc);
         launch_el(c, k_bs_r<SP>, n, sb[b], t, r, r0, w.Vh, w.R, part_hop, (const Scal *)w.sc);
         launch_fin_rows(c, k_fin_bs_beta<false>, k_fin_bs_beta<true>, w.R, 3 * w.R, part_hop, nblk_el, part_pre, w.sc,
-                        pin + (size_t)slot * w.R);
+                        pin + (size_t)slot * kPinRhs);
     };
     const double kDelta2 = w.delta2;
     int since = 0;
@@ -1706,7 +1726,7 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         since++;
         const int use = prev_ok ? slot ^ 1 : slot;
         LAPH_HIP(hipEventSynchronize(c->pin_ev[use]));
-        std::copy(pin + (size_t)use * w.R, pin + (size_t)use * w.R + w.R, hs.begin());
+        std::copy(pin + (size_t)use * kPinRhs, pin + (size_t)use * kPinRhs + w.R, hs.begin());
         prev_ok = true;
         slot ^= 1;
         // divergence: the iterated residual grew 1e4-fold above its minimum; the RHS is
@@ -1789,19 +1809,22 @@ void bicgstab_plain(Work &w, const Op<S64, GP, CP> &op, Vec xhi, Vec rhi, int ma
     const bool merged = ent_hop + ent_xr <= kMergeMost;
     static_assert(3 * kMergeMost <= 4 * kMaxBlocks, "both fit w.part");
     double *part_xr = w.part + 3 * ent_hop;
+    Scal *const pin = pinned_scal(c, kPinIter);
+    if (merged) check_every = 1;
+    bool prev_ok = false;  // (merged) the other slot holds the previous iteration's scalars
     for (int it = 0; it < maxiter;) {
-        int chunk = std::min(check_every, maxiter - it);
-        for (int k = 0; k < chunk; k++) {
-            if (merged) {
-                const int odd = (it + k) & 1;
-                op.mhat_dot(p, v, r0, w.part);
-                launch_el(c, k_merged_s, n, r, v, s, w.Vh, w.R, (const double *)w.part, ent_hop, w.sc, odd);
-                op.mhat_dot(s, t, s, w.part);
-                launch_el(c, k_merged_xr, n, xlo, p, s, t, r, r0, w.Vh, w.R, (const double *)w.part, ent_hop, part_xr,
-                          w.sc);
-                launch_el(c, k_merged_p, n, p, r, v, w.Vh, w.R, (const double *)part_xr, ent_xr, w.sc, odd);
-                continue;
-            }
+        const int chunk = std::min(check_every, maxiter - it), slot = it & 1;
+        if (merged) {
+            op.mhat_dot(p, v, r0, w.part);
+            launch_el(c, k_merged_s, n, r, v, s, w.Vh, w.R, (const double *)w.part, ent_hop, w.sc, slot);
+            op.mhat_dot(s, t, s, w.part);
+            launch_el(c, k_merged_xr, n, xlo, p, s, t, r, r0, w.Vh, w.R, (const double *)w.part, ent_hop, part_xr,
+                      w.sc);
+            launch_el(c, k_merged_p, n, p, r, v, w.Vh, w.R, (const double *)part_xr, ent_xr, w.sc, slot,
+                      pin + (size_t)slot * kPinRhs);
+            LAPH_HIP(hipEventRecord(c->pin_ev[slot], c->stream));
+        }
+        for (int k = 0; k < chunk && !merged; k++) {
             op.mhat(p, v);
             launch_red(c, k_dot<SP>, n, r0, v, w.Vh, w.R, w.part);
             launch_fin(c, k_fin_alpha, w.R, (const double *)w.part, nblk, w.R, w.sc);
@@ -1814,26 +1837,38 @@ void bicgstab_plain(Work &w, const Op<S64, GP, CP> &op, Vec xhi, Vec rhi, int ma
             launch_el(c, k_p_update<SP>, n, p, r, v, w.Vh, w.R, (const Scal *)w.sc);
         }
         it += chunk;
-        read_scal(c, w.sc, hs);
+        if (merged) {  // decisions lag one iteration behind, so the queue never drains
+            if (!prev_ok && it < maxiter) {
+                prev_ok = true;
+                continue;
+            }
+            const int use = prev_ok ? slot ^ 1 : slot;
+            LAPH_HIP(hipEventSynchronize(c->pin_ev[use]));
+            std::copy(pin + (size_t)use * kPinRhs, pin + (size_t)use * kPinRhs + w.R, hs.begin());
+        } else {
+            read_scal(c, w.sc, hs);
+        }
         // divergence: the iterated residual grew 1e4-fold above its minimum; the RHS is
         // handed to the fallback
-        bool diverged = false, any = false;
+        bool any = false;
+        unsigned drop = 0;
         int nact = 0;
         double worst = 0;
         for (int q = 0; q < w.R; q++) {
             if (!hs[q].active) continue;
             r2_min[q] = std::min(r2_min[q], hs[q].r2);
             if (!(hs[q].r2 <= 1e8 * r2_min[q])) {
-                hs[q].active = 0;
-                hs[q].breakdown = 1;
-                diverged = true;
+                drop |= 1u << q;
                 continue;
             }
             any = true;
             nact++;
             worst = std::max(worst, hs[q].tol2 > 0 ? std::sqrt(hs[q].r2 / hs[q].tol2) : 0.0);
         }
-        if (diverged) write_scal(c, w.sc, hs);
+        if (drop) {
+            hipLaunchKernelGGL(k_bs_drop, dim3(1), dim3(32), 0, c->stream, w.sc, w.R, drop);
+            LAPH_HIP(hipGetLastError());
+        }
         if (laph_verbose() && (it % 256 < check_every || !any))
             fprintf(stderr, "[laph] bicgstab it=%d active=%d/%d max |r|/target=%.3g\n", it, nact, w.R, worst);
         if (!any) break;
@@ -1934,7 +1969,7 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
     // convergence test comes one iteration later, which the rule tolerates)
     const bool lag = !plain;
     int nupd = 0;  // reliable updates (reported under LAPH_VERBOSE)
-    Scal *pin = lag ? pinned_scal(c, w.R) : nullptr;
+    Scal *const pin = pinned_scal(c, kPinIter);
     int slot = 0;
     bool prev_ok = false;  // the other slot holds the previous iteration's scalars
     auto body = [&]() {
@@ -1946,7 +1981,7 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
                             part_pre, w.sc);
             lo.mhat_dag_cg(q, to, r, (const Scal *)w.sc, part_hop);
             launch_fin_rows(c, k_fin_cg_beta<kFromPre>, k_fin_cg_beta<kFromHop>, w.R, w.R, part_hop, nblk_hop,
-                            part_pre, w.sc, 0, 1, pin + (size_t)slot * w.R);
+                            part_pre, w.sc, 0, 1, pin + (size_t)slot * kPinRhs);
         } else {
             lo.mhat(p, q);
             launch_red(c, k_normsq<SP>, n, q, w.Vh, w.R, w.part);
@@ -1967,7 +2002,7 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
             LAPH_HIP(hipEventRecord(c->pin_ev[slot], c->stream));
             const int use = prev_ok ? slot ^ 1 : slot;
             LAPH_HIP(hipEventSynchronize(c->pin_ev[use]));
-            std::copy(pin + (size_t)use * w.R, pin + (size_t)use * w.R + w.R, hs.begin());
+            std::copy(pin + (size_t)use * kPinRhs, pin + (size_t)use * kPinRhs + w.R, hs.begin());
             prev_ok = true;
             slot ^= 1;
         } else {
@@ -2084,6 +2119,14 @@ void apply_K(laph_ctx *c, const Op64 &hi, Vec xe, Vec xo, Vec oe, Vec oo)
     }
 }
 
+// totals of consecutive areas of block_partial<1> partials to the host, pin[area R + r]
+__global__ __launch_bounds__(kBS) void k_send_sums(const double *partial, int nblk, int R, double *pin)
+{
+    double s[1];
+    sum_partials<1>(partial + (size_t)blockIdx.y * nblk * R, nblk, R, blockIdx.x, s);
+    if (threadIdx.x == 0) pin[(size_t)blockIdx.y * R + blockIdx.x] = s[0];
+}
+
 // per-RHS |b - K x|^2 and |b|^2 over both parities (host result)
 void full_residual(Work &w, const Op64 &hi, Vec be, Vec bo, Vec xe, Vec xo, Vec te, Vec to, Vec re,
                    std::vector<double> &r2, std::vector<double> &b2)
@@ -2092,21 +2135,24 @@ void full_residual(Work &w, const Op64 &hi, Vec be, Vec bo, Vec xe, Vec xo, Vec 
     long n = w.Vh * w.R;
     int nblk = (int)red_blocks(n);
     apply_K(c, hi, xe, xo, te, to);
-    std::vector<double> part((size_t)nblk * w.R);
-    r2.assign(w.R, 0.0);
-    b2.assign(w.R, 0.0);
+    // the four sums' partials side by side in w.part, their totals to the host together
+    double *const pin = (double *)pinned_scal(c, kPinSums);
+    const size_t area = (size_t)nblk * w.R;
+    static_assert(4 * sizeof(double) <= sizeof(Scal), "the sums fit a slot");
     for (int par = 0; par < 2; par++) {
-        launch_red(c, k_resid64<S64>, n, par ? bo : be, par ? to : te, re, Vec{}, w.Vh, w.R, w.part, (const Scal *)w.sc,
+        double *part = w.part + 2 * par * area;
+        launch_red(c, k_resid64<S64>, n, par ? bo : be, par ? to : te, re, Vec{}, w.Vh, w.R, part, (const Scal *)w.sc,
                    1);
-        LAPH_HIP(hipMemcpyAsync(part.data(), w.part, sizeof(double) * part.size(), hipMemcpyDeviceToHost, c->stream));
-        LAPH_HIP(hipStreamSynchronize(c->stream));
-        for (int q = 0; q < w.R; q++)
-            for (int b = 0; b < nblk; b++) r2[q] += part[(size_t)b * w.R + q];
-        launch_red(c, k_normsq<S64>, n, par ? bo : be, w.Vh, w.R, w.part);
-        LAPH_HIP(hipMemcpyAsync(part.data(), w.part, sizeof(double) * part.size(), hipMemcpyDeviceToHost, c->stream));
-        LAPH_HIP(hipStreamSynchronize(c->stream));
-        for (int q = 0; q < w.R; q++)
-            for (int b = 0; b < nblk; b++) b2[q] += part[(size_t)b * w.R + q];
+        launch_red(c, k_normsq<S64>, n, par ? bo : be, w.Vh, w.R, part + area);
+    }
+    hipLaunchKernelGGL(k_send_sums, dim3(w.R, 4), dim3(kBS), 0, c->stream, (const double *)w.part, nblk, w.R, pin);
+    LAPH_HIP(hipGetLastError());
+    LAPH_HIP(hipStreamSynchronize(c->stream));
+    r2.resize(w.R);
+    b2.resize(w.R);
+    for (int q = 0; q < w.R; q++) {
+        r2[q] = pin[q] + pin[2 * w.R + q];
+        b2[q] = pin[w.R + q] + pin[3 * w.R + q];
     }
 }
 
@@ -2530,7 +2576,6 @@ void solve_batch(laph_ctx *c, const double *eta, double *x, int R, int nreal, co
         if (sv->solver == LAPH_SOLVER_BICGSTAB && !last &&
             set_active([&](int q) { return !bicg_failed[q]; }) > 0) {
             true_eo_residual(w, hi, bhat, xo, tmp, rhi, 0);
-            read_scal(c, w.sc, hs);
             bicgstab<SP, GP, CP, XP>(w, lo, hi, bhat, xo, rhi, tmp, sv->maxiter, reliable, check_every, hs);
             read_scal(c, w.sc, hs);
             for (int q = 0; q < R; q++)
