@@ -191,8 +191,7 @@ extern "C" int laph_destroy(laph_ctx_t c)
     cache_release_all(c);
     scratch_reset(c);
     if (c->pin) (void)hipHostFree(c->pin);
-    for (hipEvent_t e : c->pin_ev)
-        if (e) (void)hipEventDestroy(e);
+    if (c->pin_ev) (void)hipEventDestroy(c->pin_ev);
     for (auto &p : c->event_pool) {
         (void)hipEventDestroy(p.first);
         (void)hipEventDestroy(p.second);

@@ -187,10 +187,11 @@ struct laph_ctx {
     // tiled walk, tile_override > 0 fixes the sites per block
     int walk_mode = 0;
     int tile_override = 0;
-    // pinned host memory of the solver's scalars (slots written or read by kernels) and the
-    // events marking when a slot is complete or free again
+    // pinned host memory of the solver's scalars (slots written or read by kernels), the number
+    // of the last iteration that got a slot, and the event after the last read of a written slot
     void *pin = nullptr;
-    hipEvent_t pin_ev[3] = {nullptr, nullptr, nullptr};
+    unsigned pin_seq = 0;
+    hipEvent_t pin_ev = nullptr;
     // timing
     struct TimeAcc {
         double ms = 0, bytes = 0;

@@ -139,6 +139,29 @@ __device__ __forceinline__ void add_steps(const Dirs &dirs, int n, const Scal &s
 __device__ __forceinline__ double2 c2(Cx<double> a) { return make_double2(a.re, a.im); }
 __device__ __forceinline__ Cx<double> cx(double2 a) { return {a.x, a.y}; }
 
+// The iteration's scalars on their way to the host: its last kernel stores them to a pinned
+// slot itself and then the iteration's number beside them, which the host polls.  A copy
+// command between the kernels leaves the device idle for about 12 us on either side of it,
+// an event for some 8 us (of 45 us an iteration takes on 4^3 x 8).
+constexpr int kPinRhs = 32;  // right-hand sides of a slot
+struct PinSlot {
+    Scal s[kPinRhs];
+    unsigned seq[kPinRhs];
+};
+
+// right-hand sides r .. r + n - 1 of sc, by one whole block
+__device__ __forceinline__ void send_scal(const Scal *sc, int r, int n, PinSlot *pin, unsigned seq)
+{
+    static_assert(sizeof(Scal) % 8 == 0, "copied in 8-byte words");
+    constexpr int W = sizeof(Scal) / 8;
+    __syncthreads();
+    for (int k = threadIdx.x; k < n * W; k += kBS) ((double *)&pin->s[r])[k] = ((const double *)&sc[r])[k];
+    __threadfence_system();
+    __syncthreads();
+    if ((int)threadIdx.x < n)
+        __hip_atomic_store(&pin->seq[r + threadIdx.x], seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ------------------------------------------------------------------ BiCGStab kernels
 // r = r0 = p = convert(rhi); x = 0; partial |r|^2
 template <class SP, class XP>
@@ -486,7 +509,7 @@ __global__ __launch_bounds__(kBS) void k_merged_xr(Vec x, Vec p, Vec s, Vec t, V
 // rho_new = <r0, r>, beta = (rho_new / rho)(alpha / omega), |r|^2, convergence; p = r + beta (p - omega v)
 // (block 0 leaves a copy of the scalars in pin)
 __global__ __launch_bounds__(kBS) void k_merged_p(Vec p, Vec r, Vec v, long Vh, int R, const double *part, int ent,
-                                                  Scal *sc, int odd, Scal *pin)
+                                                  Scal *sc, int odd, PinSlot *pin, unsigned seq)
 {
     const long n = Vh * R, tid = blockIdx.x * (long)kBS + threadIdx.x;
     const int rr = (int)(threadIdx.x & (R - 1));
@@ -514,11 +537,7 @@ __global__ __launch_bounds__(kBS) void k_merged_p(Vec p, Vec r, Vec v, long Vh, 
             if (bad || done) S.active = 0;
         }
     }
-    if (blockIdx.x == 0) {
-        __syncthreads();
-        for (int k = threadIdx.x; k < R * (int)(sizeof(Scal) / 8); k += kBS)
-            ((double *)pin)[k] = ((const double *)sc)[k];
-    }
+    if (blockIdx.x == 0) send_scal(sc, 0, R, pin, seq);
     if (tid >= n || !act || bad || done) return;
 #pragma unroll
     for (int k = 0; k < 12; k++) pv[k] = rv[k] + be * (pv[k] - om * vv[k]);
@@ -930,16 +949,6 @@ __global__ __launch_bounds__(kBS) void k_bs_r(Vec s, Vec t, Vec r, Vec r0, long 
     }
 }
 
-// The iteration's scalars as its last finalisation leaves them, stored to the host's slot by
-// the kernel itself: a copy command between the kernels leaves the device idle for about 12 us
-// on either side of it (25 of the 100 us of a CG iteration on 8^3 x 16 with 32 right-hand sides)
-__device__ __forceinline__ void send_scal(const Scal &q, Scal *pin)
-{
-    static_assert(sizeof(Scal) % 8 == 0 && sizeof(Scal) / 8 <= kBS, "one 8-byte word per lane");
-    __syncthreads();
-    if (pin && threadIdx.x < sizeof(Scal) / 8) ((double *)pin)[threadIdx.x] = ((const double *)&q)[threadIdx.x];
-}
-
 // rho_new = <r0, r>, beta = (rho_new / rho)(alpha / omega), |r|^2 from the partials of
 // k_bs_r; a copy of the scalars to pin
 __device__ __forceinline__ void set_bs_beta(const double (&s)[3], Scal &q)
@@ -963,13 +972,14 @@ __device__ __forceinline__ void set_bs_beta(const double (&s)[3], Scal &q)
 }
 
 template <bool kDirect>
-__global__ __launch_bounds__(kBS) void k_fin_bs_beta(const double *partial, int nblk, int R, Scal *sc, Scal *pin)
+__global__ __launch_bounds__(kBS) void k_fin_bs_beta(const double *partial, int nblk, int R, Scal *sc, PinSlot *pin,
+                                                     unsigned seq)
 {
     const int r = blockIdx.x;
     double s[3];
     sum_rows3<kDirect>(partial, nblk, R, r, s);
     if (threadIdx.x == 0) set_bs_beta(s, sc[r]);
-    send_scal(sc[r], pin + r);
+    send_scal(sc, r, 1, pin, seq);
 }
 
 // pout = r + beta (p - omega v) with p = d.p[0]; pout may be d.p[0] or, when the owed steps
@@ -1159,7 +1169,7 @@ __device__ __forceinline__ void set_cg_beta(const double (&s)[2], Scal &q, int h
 // (pin: a copy of the scalars for the host, or null)
 template <int kFrom>
 __global__ __launch_bounds__(kBS) void k_fin_cg_beta(const double *partial, int nblk, int R, Scal *sc, int hi_conv,
-                                                     int recur, Scal *pin)
+                                                     int recur, PinSlot *pin, unsigned seq)
 {
     int r = blockIdx.x;
     double s[2];
@@ -1170,7 +1180,7 @@ __global__ __launch_bounds__(kBS) void k_fin_cg_beta(const double *partial, int 
         sum_partials<2>(partial, nblk, R, r, s);
     }
     if (threadIdx.x == 0) set_cg_beta(s, sc[r], hi_conv, recur);
-    send_scal(sc[r], pin ? pin + r : nullptr);
+    if (pin) send_scal(sc, r, 1, pin, seq);
 }
 
 // direction update pout = r + beta d_0 (real beta); pout may be d_0, the oldest direction
@@ -1542,19 +1552,50 @@ void launch_fin_rows(laph_ctx *c, K pre, K direct, int R, int nrow, const double
     launch_fin(c, pre, R, (const double *)part_pre, kChunks, R, sc, args...);
 }
 
-// Pinned slots of up to 32 right-hand sides, owned by the context: two that the iterations'
+// Pinned slots of up to kPinRhs right-hand sides, owned by the context: two that the iterations'
 // last kernels fill in turn, one for read_scal, one for write_scal, one for residual sums.
 // Kernels load and store them in place: a copy command, to or from pageable memory most of
 // all, keeps the stream idle for tens of microseconds on either side of it.
 enum { kPinIter, kPinRead = 2, kPinWrite, kPinSums, kPinSlots };
-constexpr int kPinRhs = 32;
-static Scal *pinned_scal(laph_ctx *c, int slot)
+static PinSlot *pinned_slot(laph_ctx *c, int slot)
 {
-    if (!c->pin)
-        LAPH_HIP(hipHostMalloc(&c->pin, sizeof(Scal) * kPinRhs * kPinSlots, hipHostMallocDefault));
-    for (hipEvent_t &e : c->pin_ev)
-        if (!e) LAPH_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    return (Scal *)c->pin + (size_t)slot * kPinRhs;
+    if (!c->pin) {
+        LAPH_HIP(hipHostMalloc(&c->pin, sizeof(PinSlot) * kPinSlots, hipHostMallocDefault));
+        memset(c->pin, 0, sizeof(PinSlot) * kPinSlots);
+    }
+    if (!c->pin_ev) LAPH_HIP(hipEventCreateWithFlags(&c->pin_ev, hipEventDisableTiming));
+    return (PinSlot *)c->pin + slot;
+}
+
+// an iteration's turn: its number (never 0) and the slot its last kernel fills
+struct Turn {
+    PinSlot *pin;
+    unsigned seq;
+};
+static Turn next_turn(laph_ctx *c)
+{
+    if (++c->pin_seq == 0) c->pin_seq = 2;  // (2: the slots keep alternating)
+    return {pinned_slot(c, kPinIter + (c->pin_seq & 1)), c->pin_seq};
+}
+
+// the scalars of turn t once all R right-hand sides carry its number
+static void wait_turn(laph_ctx *c, const Turn &t, int R, std::vector<Scal> &h)
+{
+    auto all = [&]() {
+        for (int r = 0; r < R; r++)
+            if (__atomic_load_n(&t.pin->seq[r], __ATOMIC_ACQUIRE) != t.seq) return false;
+        return true;
+    };
+    for (unsigned spin = 1; !all(); spin++) {
+        __builtin_ia32_pause();
+        if (spin % 65536) continue;
+        // a stream that failed, or ended without the number, must not be waited for
+        const hipError_t e = hipStreamQuery(c->stream);
+        if (e == hipErrorNotReady) continue;
+        LAPH_HIP(e);
+        LAPH_CHECK(all(), LAPH_EHIP, "an iteration ended without its scalars");
+    }
+    std::copy(t.pin->s, t.pin->s + R, h.begin());
 }
 
 __global__ __launch_bounds__(kBS) void k_move_scal(const double *from, double *to, int n)
@@ -1565,7 +1606,7 @@ __global__ __launch_bounds__(kBS) void k_move_scal(const double *from, double *t
 
 void read_scal(laph_ctx *c, const Scal *d, std::vector<Scal> &h)
 {
-    Scal *pin = pinned_scal(c, kPinRead);
+    Scal *pin = pinned_slot(c, kPinRead)->s;
     launch_el(c, k_move_scal, (long)(sizeof(Scal) / 8 * h.size()), (const double *)d, (double *)pin,
               (int)(sizeof(Scal) / 8 * h.size()));
     LAPH_HIP(hipStreamSynchronize(c->stream));
@@ -1574,12 +1615,12 @@ void read_scal(laph_ctx *c, const Scal *d, std::vector<Scal> &h)
 
 void write_scal(laph_ctx *c, Scal *d, const std::vector<Scal> &h)
 {
-    Scal *pin = pinned_scal(c, kPinWrite);
-    LAPH_HIP(hipEventSynchronize(c->pin_ev[2]));  // the kernel of the last write has read the slot
+    Scal *pin = pinned_slot(c, kPinWrite)->s;
+    LAPH_HIP(hipEventSynchronize(c->pin_ev));  // the kernel of the last write has read the slot
     std::copy(h.begin(), h.end(), pin);
     launch_el(c, k_move_scal, (long)(sizeof(Scal) / 8 * h.size()), (const double *)pin, (double *)d,
               (int)(sizeof(Scal) / 8 * h.size()));
-    LAPH_HIP(hipEventRecord(c->pin_ev[2], c->stream));
+    LAPH_HIP(hipEventRecord(c->pin_ev, c->stream));
 }
 
 // direction buffers of the fused CG loop where the solver parameters leave them open: the
@@ -1696,9 +1737,7 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         d.n = cnt;
         return d;
     };
-    Scal *const pin = pinned_scal(c, kPinIter);
-    int slot = 0;
-    bool prev_ok = false;
+    Turn turn{}, prev{};  // this iteration's and the previous one's (seq 0: none)
     auto body = [&](int b) {
         lo.mhat_dot(pb[b], v, r0, part_hop);
         launch_fin_rows(c, k_fin_bs_alpha<false>, k_fin_bs_alpha<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre, w.sc);
@@ -1707,14 +1746,14 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         launch_fin_rows(c, k_fin_bs_omega<false>, k_fin_bs_omega<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre, w.sc);
         launch_el(c, k_bs_r<SP>, n, sb[b], t, r, r0, w.Vh, w.R, part_hop, (const Scal *)w.sc);
         launch_fin_rows(c, k_fin_bs_beta<false>, k_fin_bs_beta<true>, w.R, 3 * w.R, part_hop, nblk_el, part_pre, w.sc,
-                        pin + (size_t)slot * kPinRhs);
+                        turn.pin, turn.seq);
     };
     const double kDelta2 = w.delta2;
     int since = 0;
     int why[4] = {0, 0, 0, 0};  // reliable updates by trigger: all converged, deep drop, quorum, count
     for (int it = 0; it < maxiter; it++) {
+        turn = next_turn(c);
         body(cur);
-        LAPH_HIP(hipEventRecord(c->pin_ev[slot], c->stream));
         // the direction update writes the next pair's p; with every pair owed it first
         // takes all K steps (the oldest pair is the one overwritten)
         const bool take = nowed + 1 == K;
@@ -1724,11 +1763,8 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         cur = nxt;
         nowed = take ? 0 : nowed + 1;
         since++;
-        const int use = prev_ok ? slot ^ 1 : slot;
-        LAPH_HIP(hipEventSynchronize(c->pin_ev[use]));
-        std::copy(pin + (size_t)use * kPinRhs, pin + (size_t)use * kPinRhs + w.R, hs.begin());
-        prev_ok = true;
-        slot ^= 1;
+        wait_turn(c, prev.seq ? prev : turn, w.R, hs);
+        prev = turn;
         // divergence: the iterated residual grew 1e4-fold above its minimum; the RHS is
         // handed to the fallback
         unsigned drop = 0;
@@ -1764,7 +1800,7 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
             launch_fin(c, k_fin_rho, w.R, (const double *)w.part, nblk, w.R, w.sc);
             since = 0;
             read_scal(c, w.sc, hs);
-            prev_ok = false;  // the slots predate the update
+            prev = Turn{};  // the slots predate the update
             bool left = false;
             for (int q = 0; q < w.R; q++) {
                 left |= hs[q].active != 0;
@@ -1809,20 +1845,19 @@ void bicgstab_plain(Work &w, const Op<S64, GP, CP> &op, Vec xhi, Vec rhi, int ma
     const bool merged = ent_hop + ent_xr <= kMergeMost;
     static_assert(3 * kMergeMost <= 4 * kMaxBlocks, "both fit w.part");
     double *part_xr = w.part + 3 * ent_hop;
-    Scal *const pin = pinned_scal(c, kPinIter);
     if (merged) check_every = 1;
-    bool prev_ok = false;  // (merged) the other slot holds the previous iteration's scalars
+    Turn turn{}, prev{};  // (merged) this iteration's and the previous one's (seq 0: none)
     for (int it = 0; it < maxiter;) {
-        const int chunk = std::min(check_every, maxiter - it), slot = it & 1;
+        const int chunk = std::min(check_every, maxiter - it);
         if (merged) {
+            turn = next_turn(c);
             op.mhat_dot(p, v, r0, w.part);
-            launch_el(c, k_merged_s, n, r, v, s, w.Vh, w.R, (const double *)w.part, ent_hop, w.sc, slot);
+            launch_el(c, k_merged_s, n, r, v, s, w.Vh, w.R, (const double *)w.part, ent_hop, w.sc, it & 1);
             op.mhat_dot(s, t, s, w.part);
             launch_el(c, k_merged_xr, n, xlo, p, s, t, r, r0, w.Vh, w.R, (const double *)w.part, ent_hop, part_xr,
                       w.sc);
-            launch_el(c, k_merged_p, n, p, r, v, w.Vh, w.R, (const double *)part_xr, ent_xr, w.sc, slot,
-                      pin + (size_t)slot * kPinRhs);
-            LAPH_HIP(hipEventRecord(c->pin_ev[slot], c->stream));
+            launch_el(c, k_merged_p, n, p, r, v, w.Vh, w.R, (const double *)part_xr, ent_xr, w.sc, it & 1,
+                      turn.pin, turn.seq);
         }
         for (int k = 0; k < chunk && !merged; k++) {
             op.mhat(p, v);
@@ -1838,13 +1873,8 @@ void bicgstab_plain(Work &w, const Op<S64, GP, CP> &op, Vec xhi, Vec rhi, int ma
         }
         it += chunk;
         if (merged) {  // decisions lag one iteration behind, so the queue never drains
-            if (!prev_ok && it < maxiter) {
-                prev_ok = true;
-                continue;
-            }
-            const int use = prev_ok ? slot ^ 1 : slot;
-            LAPH_HIP(hipEventSynchronize(c->pin_ev[use]));
-            std::copy(pin + (size_t)use * kPinRhs, pin + (size_t)use * kPinRhs + w.R, hs.begin());
+            wait_turn(c, prev.seq ? prev : turn, w.R, hs);
+            prev = turn;
         } else {
             read_scal(c, w.sc, hs);
         }
@@ -1969,9 +1999,7 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
     // convergence test comes one iteration later, which the rule tolerates)
     const bool lag = !plain;
     int nupd = 0;  // reliable updates (reported under LAPH_VERBOSE)
-    Scal *const pin = pinned_scal(c, kPinIter);
-    int slot = 0;
-    bool prev_ok = false;  // the other slot holds the previous iteration's scalars
+    Turn turn{}, prev{};  // this iteration's and the previous one's (seq 0: none)
     auto body = [&]() {
         if constexpr (!plain) {
             // M p with |q|^2 and A^-1 gamma_5 q from its epilogue; M^dag q feeding the CG
@@ -1981,30 +2009,27 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
                             part_pre, w.sc);
             lo.mhat_dag_cg(q, to, r, (const Scal *)w.sc, part_hop);
             launch_fin_rows(c, k_fin_cg_beta<kFromPre>, k_fin_cg_beta<kFromHop>, w.R, w.R, part_hop, nblk_hop,
-                            part_pre, w.sc, 0, 1, pin + (size_t)slot * kPinRhs);
+                            part_pre, w.sc, 0, 1, turn.pin, turn.seq);
         } else {
             lo.mhat(p, q);
             launch_red(c, k_normsq<SP>, n, q, w.Vh, w.R, w.part);
             launch_fin(c, k_fin_cg_alpha<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc);
             lo.mhat_dag(q, y, to);
             launch_red(c, k_cg_update<SP, XP, true>, n, xlo, p, res, q, r, y, w.Vh, w.R, w.part, (const Scal *)w.sc);
-            launch_fin(c, k_fin_cg_beta<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc, 1, 0, (Scal *)nullptr);
+            launch_fin(c, k_fin_cg_beta<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc, 1, 0, (PinSlot *)nullptr, 0u);
             launch_el(c, k_cg_p<SP, XP>, n, p, owed_dirs(0, 1), r, xlo, w.Vh, w.R, (const Scal *)w.sc, 0, 0);
         }
     };
     for (int it = 0; it < maxiter;) {
         int chunk = std::min(check_every, maxiter - it);
+        if (lag) turn = next_turn(c);
         for (int k = 0; k < chunk; k++) body();
         it += chunk;
         since += chunk;
         step_now = fuse;
         if (lag) {
-            LAPH_HIP(hipEventRecord(c->pin_ev[slot], c->stream));
-            const int use = prev_ok ? slot ^ 1 : slot;
-            LAPH_HIP(hipEventSynchronize(c->pin_ev[use]));
-            std::copy(pin + (size_t)use * kPinRhs, pin + (size_t)use * kPinRhs + w.R, hs.begin());
-            prev_ok = true;
-            slot ^= 1;
+            wait_turn(c, prev.seq ? prev : turn, w.R, hs);
+            prev = turn;
         } else {
             read_scal(c, w.sc, hs);
         }
@@ -2044,7 +2069,7 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
             orth = true;  // the direction update makes p orthogonal to the new r
             since = 0;
             read_scal(c, w.sc, hs);
-            prev_ok = false;  // the slots predate the update
+            prev = Turn{};  // the slots predate the update
             bool left = false;
             for (int k = 0; k < w.R; k++) {
                 left |= hs[k].active != 0;
@@ -2136,7 +2161,7 @@ void full_residual(Work &w, const Op64 &hi, Vec be, Vec bo, Vec xe, Vec xo, Vec 
     int nblk = (int)red_blocks(n);
     apply_K(c, hi, xe, xo, te, to);
     // the four sums' partials side by side in w.part, their totals to the host together
-    double *const pin = (double *)pinned_scal(c, kPinSums);
+    double *const pin = (double *)pinned_slot(c, kPinSums)->s;
     const size_t area = (size_t)nblk * w.R;
     static_assert(4 * sizeof(double) <= sizeof(Scal), "the sums fit a slot");
     for (int par = 0; par < 2; par++) {
