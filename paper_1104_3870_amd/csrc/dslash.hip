@@ -164,32 +164,38 @@ __device__ __forceinline__ Cx<double> unit_mul(double ur, double ui, Cx<double> 
     return {ur * z.re - ui * z.im, ur * z.im + ui * z.re};
 }
 
+// checkerboard index of the neighbour in direction d
+__device__ __forceinline__ long neighbour(const DslashArgs &P, int d, int x, int y, int z, int t)
+{
+    const int mu = d >> 1, st = d & 1 ? -1 : 1, ns = P.ns;
+    auto wrap = [](int a, int m) { return a < 0 ? a + m : a >= m ? a - m : a; };
+    if (mu == 0) x = wrap(x + st, ns);
+    if (mu == 1) y = wrap(y + st, ns);
+    if (mu == 2) z = wrap(z + st, ns);
+    if (mu == 3) t = wrap(t + st, P.nt);
+    return lex_index(x, y, z, t, ns) >> 1;
+}
+
 // hop(o0, o1, q, sb, sw) gets the link of direction d times the two colour vectors of the
 // neighbour's projected half spinor, hop weight and boundary factor included, and what the
 // lower components take of them: acc2 += sb b2 (sw ? o1 : o0), acc3 += sb b3 (sw ? o0 : o1)
-template <bool O32, class F>
-__device__ __forceinline__ void hop_dir(const DslashArgs &P, int d, long i, int r, int x, int y, int z, int t, F hop)
+// kStage: staged are the nine link elements of this site and direction in LDS, as the product
+// takes them (else they are read from the field)
+template <bool O32, bool kStage, class F>
+__device__ __forceinline__ void hop_dir(const DslashArgs &P, int d, long i, int r, int x, int y, int z, int t,
+                                        const double2 *staged, F hop)
 {
     // (a table of the function's own: a shared one costs the rolled kernel 36 registers)
     constexpr HopCoef kc[4] = {hop_coef(0), hop_coef(1), hop_coef(2), hop_coef(3)};
-    const int R = P.R, ns = P.ns, nt = P.nt, par = P.par;
+    const int R = P.R, par = P.par;
     const long Vh = P.Vh;
     const double2 *in = (const double2 *)P.in;
     const double2 *g = (const double2 *)P.gauge;
     const int mu = d >> 1;
     const bool fwd = !(d & 1);
-    const int st = fwd ? 1 : -1;
-    int xx = x, yy = y, zz = z, tt = t;
     double w = mu == 3 ? P.wt : P.ws;
-    auto wrap = [](int a, int m) { return a < 0 ? a + m : a >= m ? a - m : a; };
-    if (mu == 0) xx = wrap(x + st, ns);
-    if (mu == 1) yy = wrap(y + st, ns);
-    if (mu == 2) zz = wrap(z + st, ns);
-    if (mu == 3) {
-        tt = wrap(t + st, nt);
-        if (fwd ? t + 1 == nt : t == 0) w *= P.bct;
-    }
-    const long nb = lex_index(xx, yy, zz, tt, ns) >> 1;
+    if (mu == 3 && (fwd ? t + 1 == P.nt : t == 0)) w *= P.bct;
+    const long nb = neighbour(P, d, x, y, z, t);
     Spin<double> s;
     load_spinor<S64, O32>(in, nullptr, Vh, R, nb, r, s);
     // U_mu(x), or for the backward hop U_mu(x - mu)^dag: planes read transposed, conjugated
@@ -197,10 +203,12 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &P, int d, long i, int 
     const long li = fwd ? i : nb;
     const double cj = fwd ? 1.0 : -1.0;
     Cx<double> U[9];
+    if constexpr (!kStage) {
 #pragma unroll
-    for (int k = 0; k < 9; k++) {
-        const double2 v = elem<O32>(gp + (long)(fwd ? k : (k % 3) * 3 + k / 3) * Vh, li);
-        U[k] = {v.x, cj * v.y};
+        for (int k = 0; k < 9; k++) {
+            const double2 v = elem<O32>(gp + (long)(fwd ? k : (k % 3) * 3 + k / 3) * Vh, li);
+            U[k] = {v.x, cj * v.y};
+        }
     }
     const HopCoef &q = kc[mu];
     const double sa = fwd ? w : -w, sb = fwd ? 1.0 : -1.0;
@@ -211,18 +219,23 @@ __device__ __forceinline__ void hop_dir(const DslashArgs &P, int d, long i, int 
         h0[c] = w * s.v[0][c] + unit_mul(sa * q.a0r, sa * q.a0i, sw ? s.v[3][c] : s.v[2][c]);
         h1[c] = w * s.v[1][c] + unit_mul(sa * q.a1r, sa * q.a1i, sw ? s.v[2][c] : s.v[3][c]);
     }
+    if constexpr (kStage) {
+        // (not before the spinor is used up: the registers of both cost a wave per SIMD)
+#pragma unroll
+        for (int k = 0; k < 9; k++) U[k] = {staged[k].x, staged[k].y};
+    }
     mat_vec(U, h0, o0);
     mat_vec(U, h1, o1);
     hop(o0, o1, q, sb, sw);
 }
 
-template <bool O32>
+template <bool O32, bool kStage>
 __device__ __forceinline__ void hop_rolled(const DslashArgs &P, long i, int r, int x, int y, int z, int t,
-                                           Spin<double> &acc)
+                                           const double2 *staged, Spin<double> &acc)
 {
 #pragma unroll 1
     for (int d = 0; d < 8; d++)
-        hop_dir<O32>(P, d, i, r, x, y, z, t,
+        hop_dir<O32, kStage>(P, d, i, r, x, y, z, t, kStage ? staged + 9 * d : nullptr,
                      [&](const Cx<double> (&o0)[3], const Cx<double> (&o1)[3], const HopCoef &q, double sb, bool sw) {
 #pragma unroll
             for (int c = 0; c < 3; c++) {
@@ -270,7 +283,13 @@ __device__ __forceinline__ void wave_sum_rhs(double (&q)[3], int R)
         for (int k = 0; k < 3; k++) q[k] += __shfl_xor(q[k], off, 64);
 }
 
-template <class SP, class GP, class CP, int MODE, bool O32>
+// kStage (R = 8, 16 or 32 right-hand sides: a block holds 256 / R whole sites): the block's
+// links and clover elements go through LDS.  Read per lane they are half of the bytes the
+// vector cache returns although all R lanes of a site read the same ones, and that return
+// path, 90% busy, bound the kernel.  24^3 x 32, R = 32: 1.50 -> 1.16 ms (1.13 with the
+// walk's tiles below, 4.8 TB/s of the traffic behind L2); 16^3 x 32: 458 -> 363 us;
+// R = 16: 799 -> 610, R = 8 on 16^3 x 32: 135 -> 119 us.
+template <class SP, class GP, class CP, int MODE, bool O32, bool kStage>
 __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
 {
     using A = typename SP::A;
@@ -280,8 +299,8 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
     const long Vh = P.Vh;
     constexpr bool kDot = MODE == M_INV_AFTER_DOT;
     const bool valid = tid < Vh * R;
-    if (!kDot && !valid) return;
-    if (kDot && !valid) tid = Vh * R - 1;  // (lanes past the end take part in the sums, with zeros)
+    if (!kDot && !kStage && !valid) return;
+    if (!valid) tid = Vh * R - 1;  // (lanes past the end take part in the staging and the sums, with zeros)
     // 32-bit lane arithmetic: the launcher guarantees Vh R < 2^28
     const unsigned pos = (unsigned)tid / (unsigned)R;
     const int r = (int)((unsigned)tid - pos * (unsigned)R);
@@ -294,8 +313,39 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
         i = pos;
         cb_coords(i, par, ns, x, y, z, t);
     }
-    const auto *in = (const typename SP::E *)P.in;
-    const auto *g = (const typename GP::E *)P.gauge;
+    extern __shared__ double2 stage[];  // [site][8][9] links, then [site][72] clover elements
+    const double2 *staged = nullptr;
+    const auto *cl = (const typename CP::E *)P.clov;
+    long cl_plane = Vh, cl_site = i;
+    if constexpr (kStage) {
+        const int S = 256 / R, s = threadIdx.x & (S - 1), e0 = threadIdx.x / S;  // (sites fastest: coalesced)
+        const unsigned sp = min(b * (unsigned)S + s, (unsigned)Vh - 1);
+        int sx, sy, sz, st;
+        long si;
+        if (P.wby) {
+            si = walk_coords(sp, ns, nt, par, P.wby, P.wbz, sx, sy, sz, st);
+        } else {
+            si = sp;
+            cb_coords(si, par, ns, sx, sy, sz, st);
+        }
+        double *clov = (double *)(stage + 72 * S);
+        const double2 *g = (const double2 *)P.gauge;
+#pragma unroll 3
+        for (int e = e0; e < 72; e += R) {
+            const int d = e / 9, k = e - 9 * d;
+            const bool back = d & 1;
+            const long li = back ? neighbour(P, d, sx, sy, sz, st) : si;
+            const double2 v = elem<O32>(g + ((long)((d >> 1) * 2 + (back ? opar : par)) * 9 +
+                                             (back ? (k % 3) * 3 + k / 3 : k)) * Vh, li);
+            stage[72 * s + e] = make_double2(v.x, back ? -v.y : v.y);
+            if constexpr (MODE != M_PLAIN) clov[72 * s + e] = elem<O32>((const double *)P.clov + (long)e * Vh, si);
+        }
+        __syncthreads();
+        staged = stage + 72 * (threadIdx.x / R);
+        cl = (const typename CP::E *)clov + 72 * (threadIdx.x / R);
+        cl_plane = 1;
+        cl_site = 0;
+    }
 
     Spin<A> acc;
 #pragma unroll
@@ -303,7 +353,7 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
 #pragma unroll
         for (int c = 0; c < 3; c++) acc.v[a][c] = {(A)0, (A)0};
 
-    hop_rolled<O32>(P, i, r, x, y, z, t, acc);
+    hop_rolled<O32, kStage>(P, i, r, x, y, z, t, staged, acc);
 
     if (P.g5d) {
 #pragma unroll
@@ -314,7 +364,6 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
     }
 
     const A ca = (A)P.a, cc = (A)P.c;
-    const auto *cl = (const typename CP::E *)P.clov;
     Spin<A> res;
     if constexpr (MODE == M_PLAIN) {
 #pragma unroll
@@ -331,7 +380,7 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
         }
     } else if constexpr (MODE == M_INV_AFTER || kDot) {
         Spin<A> m;
-        clover_mul<CP, A, O32>(cl, Vh, i, acc, m);
+        clover_mul<CP, A, O32>(cl, cl_plane, cl_site, acc, m);
 #pragma unroll
         for (int a = 0; a < 4; a++)
 #pragma unroll
@@ -351,11 +400,11 @@ __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
         for (int a = 0; a < 4; a++)
 #pragma unroll
             for (int c = 0; c < 3; c++) sum.v[a][c] = ca * xv.v[a][c] + cc * acc.v[a][c];
-        clover_mul<CP, A, O32>(cl, Vh, i, sum, res);
+        clover_mul<CP, A, O32>(cl, cl_plane, cl_site, sum, res);
     } else {  // M_CLOV_ADD
         Spin<A> xv, m;
         load_spinor<SP, O32>((const typename SP::E *)P.x, P.x_nrm, Vh, R, i, r, xv);
-        clover_mul<CP, A, O32>(cl, Vh, i, xv, m);
+        clover_mul<CP, A, O32>(cl, cl_plane, cl_site, xv, m);
 #pragma unroll
         for (int a = 0; a < 4; a++)
 #pragma unroll
@@ -459,7 +508,7 @@ __global__ __launch_bounds__(12 * kSplit) void k_dslash_split(const DslashArgs P
         yv = {e.x, e.y};
     }
     if (w < 8)
-        hop_dir<true>(P, w, i, r, x, y, z, t,
+        hop_dir<true, false>(P, w, i, r, x, y, z, t, nullptr,
                       [&](const Cx<double> (&o0)[3], const Cx<double> (&o1)[3], const HopCoef &, double, bool) {
 #pragma unroll
             for (int c = 0; c < 3; c++) {
@@ -551,15 +600,19 @@ double dslash_bytes(long Vh, int R, int gbytes, int cbytes, int sbytes, bool has
     return (double)Vh * (site + R * per_rhs);
 }
 
-template <class SP, class GP, class CP, bool O32>
-void launch_modes(int mode, dim3 grid, dim3 block, hipStream_t st, const DslashArgs &a)
+template <class SP, class GP, class CP, bool kStage>
+void launch_modes(int mode, dim3 grid, dim3 block, size_t lds, hipStream_t st, const DslashArgs &a)
 {
     switch (mode) {
-    case M_PLAIN: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_PLAIN, O32>), grid, block, 0, st, a); break;
-    case M_INV_AFTER: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER, O32>), grid, block, 0, st, a); break;
-    case M_INV_OF_SUM: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_OF_SUM, O32>), grid, block, 0, st, a); break;
-    case M_INV_AFTER_DOT: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER_DOT, O32>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_CLOV_ADD, O32>), grid, block, 0, st, a); break;
+    case M_PLAIN: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_PLAIN, true, kStage>), grid, block, lds, st, a); break;
+    case M_INV_AFTER: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER, true, kStage>), grid, block, lds, st, a); break;
+    case M_INV_OF_SUM: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_OF_SUM, true, kStage>), grid, block, lds, st, a); break;
+    case M_INV_AFTER_DOT:
+        if constexpr (!kStage) {
+            hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER_DOT, true, false>), grid, block, lds, st, a);
+            break;
+        }
+    default: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_CLOV_ADD, true, kStage>), grid, block, lds, st, a); break;
     }
 }
 
@@ -599,17 +652,21 @@ void launch_dslash(laph_ctx *c, int mode, const DslashArgs &a, hipStream_t st)
                "%d FP64 fields of %ld sites exceed the hopping kernel's 32-bit offsets", a.R, a.Vh);
     // many right-hand sides per site: a site's records span R x 192 B, so the time
     // neighbours of checkerboard order (Ns^3 / 2 sites away) fall out of L2; walk tiles
-    // through time instead (3 x 3 where Ns allows it, else 2 x 2)
+    // through time instead, the largest of which three slices stay in L2 (24^3 x 32, R = 32,
+    // staged: 12 x 12 1.22, 6 x 6 1.13, 3 x 3 1.16, 2 x 2 1.28 ms; 16^3 x 32: 4 x 4 363, 2 x 2 382 us)
     DslashArgs b = a;
     b.wby = b.wbz = 0;
-    if (a.R >= 8) b.wby = b.wbz = (a.ns % 3 == 0) ? 3 : 2;
+    if (a.R >= 8) b.wby = b.wbz = a.ns % 6 == 0 ? 6 : a.ns % 4 == 0 ? 4 : 2;
     b.m_R = umulhi_magic(a.R);  // (exact: every index is below kSplitMost)
     b.m_nsh = umulhi_magic(a.ns / 2);
     b.m_ns = umulhi_magic(a.ns);
     if (n <= kSplitMost)
         launch_split(mode, n, st, b);
+    else if (mode != M_INV_AFTER_DOT && (a.R == 8 || a.R == 16 || a.R == 32))
+        launch_modes<SP, GP, CP, true>(mode, grid, block, (size_t)(256 / a.R) * 72 * (sizeof(double2) + sizeof(double)),
+                                       st, b);
     else
-        launch_modes<SP, GP, CP, true>(mode, grid, block, st, b);
+        launch_modes<SP, GP, CP, false>(mode, grid, block, 0, st, b);
     LAPH_HIP(hipGetLastError());
     bool has_x = a.x != nullptr && (mode != M_PLAIN || a.x);
     if (e0)
