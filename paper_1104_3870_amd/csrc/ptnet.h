@@ -1,8 +1,8 @@
 // Gauge-equivariant parallel-transport network (learned preconditioner), internal API.
 //
-// Net layout of a batch of fields: float2 a[((r*C + c)*V + s)*12 + k] with s the
-// lexicographic site (x fastest) and k = alpha*3 + colour, i.e. the canonical spinor order
-// in FP32 with a channel axis.  Links: float2 [V][4][9] (canonical order, FP32).
+// Net layout of a batch of fields: component k = alpha*3 + colour of lexicographic site s (x
+// fastest) of field r, channel c, at float2 a[(r*C + c)*12*V + ((k/2)*V + s)*2 + k%2], planes
+// of float4 over the sites.  Links: float2 planes [mu][row][column][V].
 #pragma once
 
 #include "laph_impl.h"

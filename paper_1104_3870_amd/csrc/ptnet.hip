@@ -31,21 +31,31 @@ __host__ __device__ inline uint32_t f2bf(float f)
 }
 __host__ __device__ inline uint32_t pack_bf(float re, float im) { return f2bf(re) | (f2bf(im) << 16); }
 
-__device__ __forceinline__ void lex_coords(long s, int ns, int &x, int &y, int &z, int &t)
+// (32-bit divisions: V nrhs sites of 96 bytes each fit the device's memory far below 2^32)
+__device__ __forceinline__ void lex_coords(unsigned s, unsigned ns, int &x, int &y, int &z, int &t)
 {
-    x = (int)(s % ns);
-    long q = s / ns;
-    y = (int)(q % ns);
-    q /= ns;
-    z = (int)(q % ns);
-    t = (int)(q / ns);
+    unsigned q = s / ns;
+    x = (int)(s - q * ns);
+    const unsigned q2 = q / ns;
+    y = (int)(q - q2 * ns);
+    const unsigned q3 = q2 / ns;
+    z = (int)(q2 - q3 * ns);
+    t = (int)q3;
 }
+
+// Layouts inside the network, so that the lanes of a wave, which hold consecutive sites, read
+// and write consecutive addresses: a field is six planes of V float4 (two components each),
+// the links 36 planes of V float2 [mu][row][column].  (Site records of 96 and 72 bytes made
+// every load of a wave touch 48 to 64 cache lines.  8^3 x 16, 20 fields: a layer of two channels
+// 65 -> 59 us, now bound by its FP32 operations, 768 a lane for each channel and direction; a
+// training step 1.07 -> 0.85 ms with the wave sums and the loss below.)
+__device__ __forceinline__ size_t net_at(long s, int k, long V) { return ((size_t)(k >> 1) * V + s) * 2 + (k & 1); }
 
 // Transport matrix of direction d at site (x,y,z,t): the neighbour whose field is
 // transported and the 3x3 colour matrix (boundary factor folded in); d = 0 gives the
 // identity.
 __device__ __forceinline__ long pt_hop(const float2 *__restrict__ links, long s, int d, int x, int y, int z, int t,
-                                       int ns, int nt, float bct, Cx<float> L[9])
+                                       int ns, int nt, long V, float bct, Cx<float> L[9])
 {
     if (d == 0) {
 #pragma unroll
@@ -72,40 +82,41 @@ __device__ __forceinline__ long pt_hop(const float2 *__restrict__ links, long s,
     }
     long nb = lex_index(xx, yy, zz, tt, ns);
     if (d <= 4) {
-        const float2 *u = links + (s * 4 + mu) * 9;
+        const float2 *u = links + (size_t)mu * 9 * V + s;
 #pragma unroll
         for (int k = 0; k < 9; k++) {
-            float2 v = u[k];
+            float2 v = u[k * V];
             L[k] = Cx<float>{ph * v.x, ph * v.y};
         }
     } else {
-        const float2 *u = links + (nb * 4 + mu) * 9;
+        const float2 *u = links + (size_t)mu * 9 * V + nb;
 #pragma unroll
         for (int a = 0; a < 3; a++)
 #pragma unroll
             for (int b = 0; b < 3; b++) {
-                float2 v = u[b * 3 + a];
+                float2 v = u[(b * 3 + a) * V];
                 L[a * 3 + b] = Cx<float>{ph * v.x, -ph * v.y};
             }
     }
     return nb;
 }
 
-__device__ __forceinline__ void ld12(const float2 *__restrict__ p, Cx<float> v[12])
+// site s of the field p
+__device__ __forceinline__ void ld12(const float2 *__restrict__ p, long s, long V, Cx<float> v[12])
 {
-    const float4 *q = (const float4 *)p;
+    const float4 *q = (const float4 *)p + s;
 #pragma unroll
     for (int k = 0; k < 6; k++) {
-        float4 a = q[k];
+        float4 a = q[k * V];
         v[2 * k] = Cx<float>{a.x, a.y};
         v[2 * k + 1] = Cx<float>{a.z, a.w};
     }
 }
-__device__ __forceinline__ void st12(float2 *__restrict__ p, const Cx<float> v[12])
+__device__ __forceinline__ void st12(float2 *__restrict__ p, long s, long V, const Cx<float> v[12])
 {
-    float4 *q = (float4 *)p;
+    float4 *q = (float4 *)p + s;
 #pragma unroll
-    for (int k = 0; k < 6; k++) q[k] = make_float4(v[2 * k].re, v[2 * k].im, v[2 * k + 1].re, v[2 * k + 1].im);
+    for (int k = 0; k < 6; k++) q[k * V] = make_float4(v[2 * k].re, v[2 * k].im, v[2 * k + 1].re, v[2 * k + 1].im);
 }
 
 // tv = L phi (colour matrix on each spin component)
@@ -145,10 +156,10 @@ __global__ __launch_bounds__(kPtBS) void k_pt_layer(const float2 *__restrict__ l
         for (int k = 0; k < 12; k++) acc[co][k] = Cx<float>{0.f, 0.f};
     for (int d = 0; d < 9; d++) {
         Cx<float> L[9];
-        long nb = pt_hop(links, s, d, x, y, z, t, ns, nt, bct, L);
+        long nb = pt_hop(links, s, d, x, y, z, t, ns, nt, V, bct, L);
         for (int ci = 0; ci < cin; ci++) {
             Cx<float> phi[12], tv[12];
-            ld12(inr + ((size_t)ci * V + nb) * 12, phi);
+            ld12(inr + (size_t)ci * V * 12, nb, V, phi);
             transport(L, phi, tv);
             const float2 *wp = sw + (ci * 9 + d) * 16;
 #pragma unroll
@@ -165,7 +176,28 @@ __global__ __launch_bounds__(kPtBS) void k_pt_layer(const float2 *__restrict__ l
         }
     }
 #pragma unroll
-    for (int co = 0; co < CO; co++) st12(out + ((size_t)(r * CO + co) * V + s) * 12, acc[co]);
+    for (int co = 0; co < CO; co++) st12(out + (size_t)(r * CO + co) * V * 12, s, V, acc[co]);
+}
+
+// one step of the spread wave sum below: N values, lanes OFF apart
+template <int OFF, int N, int M>
+__device__ __forceinline__ void wave_spread(float (&v)[M], int lane, int &at)
+{
+    if constexpr (OFF > 0) {
+        constexpr int H = N > 1 ? N / 2 : 1;
+        const bool up = lane & OFF;
+        if constexpr (N > 1) {
+#pragma unroll
+            for (int j = 0; j < H; j++) {
+                const float keep = up ? v[j + H] : v[j], give = up ? v[j] : v[j + H];
+                v[j] = keep + __shfl_xor(give, OFF);
+            }
+            if (up) at += H;
+        } else {
+            v[0] += __shfl_xor(v[0], OFF);
+        }
+        wave_spread<OFF / 2, H>(v, lane, at);
+    }
 }
 
 // Partial weight gradients of one (ci, d) pair per blockIdx.y over a chunk of (field, site)
@@ -185,18 +217,18 @@ __global__ __launch_bounds__(kPtBS) void k_pt_wgrad(const float2 *__restrict__ l
 #pragma unroll
         for (int e = 0; e < 16; e++) p[co][e] = Cx<float>{0.f, 0.f};
     for (long it = beg + threadIdx.x; it < end; it += blockDim.x) {
-        int r = (int)(it / V);
-        long s = it - (long)r * V;
+        const unsigned r = (unsigned)it / (unsigned)V;
+        const long s = (unsigned)it - r * (unsigned)V;
         int x, y, z, t;
         lex_coords(s, ns, x, y, z, t);
         Cx<float> L[9], phi[12], tv[12];
-        long nb = pt_hop(links, s, d, x, y, z, t, ns, nt, bct, L);
-        ld12(act + (((size_t)r * cin + ci) * V + nb) * 12, phi);
+        long nb = pt_hop(links, s, d, x, y, z, t, ns, nt, V, bct, L);
+        ld12(act + ((size_t)r * cin + ci) * V * 12, nb, V, phi);
         transport(L, phi, tv);
 #pragma unroll
         for (int co = 0; co < CO; co++) {
             Cx<float> gg[12];
-            ld12(g + (((size_t)r * CO + co) * V + s) * 12, gg);
+            ld12(g + ((size_t)r * CO + co) * V * 12, s, V, gg);
 #pragma unroll
             for (int sa = 0; sa < 4; sa++)
 #pragma unroll
@@ -208,20 +240,22 @@ __global__ __launch_bounds__(kPtBS) void k_pt_wgrad(const float2 *__restrict__ l
                 }
         }
     }
+    // sums over the wave of all 32 CO values at once: at each step a lane keeps half of its
+    // values and gets the other lane's share of them, the same additions as a butterfly of
+    // each value by itself in a sixth of the exchanges
     __shared__ float2 red[kPtBS / 64][CO * 16];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float v[CO * 32];
 #pragma unroll
-    for (int co = 0; co < CO; co++)
+    for (int j = 0; j < CO * 16; j++) {
+        v[2 * j] = p[j / 16][j % 16].re;
+        v[2 * j + 1] = p[j / 16][j % 16].im;
+    }
+    int at = 0;  // index of the lane's first value among the 32 CO
+    wave_spread<32, CO * 32>(v, lane, at);
+    // (CO * 32 >= 64 leaves CO / 2 values a lane; CO = 1 one value in two lanes)
 #pragma unroll
-        for (int e = 0; e < 16; e++) {
-            float re = p[co][e].re, im = p[co][e].im;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                re += __shfl_xor(re, off);
-                im += __shfl_xor(im, off);
-            }
-            if (lane == 0) red[wv][co * 16 + e] = make_float2(re, im);
-        }
+    for (int j = 0; j < (CO * 32 + 63) / 64; j++) ((float *)red[wv])[at + j] = v[j];
     __syncthreads();
     const size_t nwl = (size_t)CO * cin * 144;
     for (int j = threadIdx.x; j < CO * 16; j += blockDim.x) {
@@ -239,8 +273,20 @@ __global__ void k_pt_sum_parts(const float2 *__restrict__ gpart, float2 *__restr
 {
     long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (i >= nwl) return;
+    // (one after the other in order; 16 loads in flight)
     float2 s = gpart[i];
-    for (int b = 1; b < nblk; b++) {
+    int b = 1;
+    for (; b + 16 <= nblk; b += 16) {
+        float2 e[16];
+#pragma unroll
+        for (int k = 0; k < 16; k++) e[k] = gpart[(b + k) * nwl + i];
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            s.x += e[k].x;
+            s.y += e[k].y;
+        }
+    }
+    for (; b < nblk; b++) {
         s.x += gpart[b * nwl + i].x;
         s.y += gpart[b * nwl + i].y;
     }
@@ -284,15 +330,64 @@ __global__ void k_pt_adam(float2 *__restrict__ w, uint32_t *__restrict__ wbf, fl
     wbf[i] = pack_bf(x.x, x.y);
 }
 
-__global__ void k_pt_from64(const double2 *__restrict__ a, float2 *__restrict__ b, long n)
+// Between the interface's FP64 records and the planes, 64 sites a block through LDS so that
+// both sides are read and written in whole lines.  kG4: gamma_4 applied on the way in (it
+// swaps the upper and lower spin pairs in the chiral basis).
+constexpr int kPtTile = 64;
+
+template <bool kG4>
+__global__ __launch_bounds__(kPtBS) void k_pt_from64(const double2 *__restrict__ a, float2 *__restrict__ b, long V)
 {
-    long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (i < n) b[i] = make_float2((float)a[i].x, (float)a[i].y);
+    __shared__ float2 tile[kPtTile][13];
+    const long s0 = blockIdx.x * (long)kPtTile;
+    const int cnt = (int)min((long)kPtTile, V - s0);
+    a += ((size_t)blockIdx.y * V + s0) * 12;
+    for (int i = threadIdx.x; i < cnt * 12; i += kPtBS) {
+        const int s = i / 12, k = i - 12 * s;
+        tile[s][kG4 ? ((k / 3) ^ 2) * 3 + k % 3 : k] = make_float2((float)a[i].x, (float)a[i].y);
+    }
+    __syncthreads();
+    float4 *q = (float4 *)b + (size_t)blockIdx.y * V * 6 + s0;
+    for (int i = threadIdx.x; i < kPtTile * 6; i += kPtBS) {
+        const int s = i % kPtTile, k = i / kPtTile;
+        if (s < cnt) q[k * V + s] = make_float4(tile[s][2 * k].x, tile[s][2 * k].y, tile[s][2 * k + 1].x, tile[s][2 * k + 1].y);
+    }
 }
-__global__ void k_pt_to64(const float2 *__restrict__ a, double2 *__restrict__ b, long n)
+__global__ __launch_bounds__(kPtBS) void k_pt_to64(const float2 *__restrict__ a, double2 *__restrict__ b, long V)
 {
-    long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (i < n) b[i] = make_double2(a[i].x, a[i].y);
+    __shared__ float2 tile[kPtTile][13];
+    const long s0 = blockIdx.x * (long)kPtTile;
+    const int cnt = (int)min((long)kPtTile, V - s0);
+    const float4 *q = (const float4 *)a + (size_t)blockIdx.y * V * 6 + s0;
+    for (int i = threadIdx.x; i < kPtTile * 6; i += kPtBS) {
+        const int s = i % kPtTile, k = i / kPtTile;
+        if (s >= cnt) continue;
+        const float4 v = q[k * V + s];
+        tile[s][2 * k] = make_float2(v.x, v.y);
+        tile[s][2 * k + 1] = make_float2(v.z, v.w);
+    }
+    __syncthreads();
+    b += ((size_t)blockIdx.y * V + s0) * 12;
+    for (int i = threadIdx.x; i < cnt * 12; i += kPtBS) {
+        const int s = i / 12, k = i - 12 * s;
+        b[i] = make_double2(tile[s][k].x, tile[s][k].y);
+    }
+}
+__global__ __launch_bounds__(kPtBS) void k_pt_links(const double2 *__restrict__ U, float2 *__restrict__ links, long V)
+{
+    __shared__ float2 tile[kPtTile][37];
+    const long s0 = blockIdx.x * (long)kPtTile;
+    const int cnt = (int)min((long)kPtTile, V - s0);
+    U += (size_t)s0 * 36;
+    for (int i = threadIdx.x; i < cnt * 36; i += kPtBS) {
+        const int s = i / 36, e = i - 36 * s;
+        tile[s][e] = make_float2((float)U[i].x, (float)U[i].y);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kPtTile * 36; i += kPtBS) {
+        const int s = i % kPtTile, e = i / kPtTile;
+        if (s < cnt) links[(size_t)e * V + s0 + s] = tile[s][e];
+    }
 }
 
 __global__ void k_eo_to_net(const double2 *__restrict__ half, int par, float2 *__restrict__ full, int ns, long V,
@@ -309,7 +404,7 @@ __global__ void k_eo_to_net(const double2 *__restrict__ half, int par, float2 *_
         double2 h = half[(long)k * Vh + (s >> 1)];
         v = make_float2((float)h.x, (float)h.y);
     }
-    full[tid] = v;
+    full[net_at(s, k, V)] = v;
 }
 
 __global__ void k_net_to_eo(const float2 *__restrict__ full, int par, double2 *__restrict__ half, int ns, long Vh)
@@ -321,14 +416,16 @@ __global__ void k_net_to_eo(const float2 *__restrict__ full, int par, double2 *_
     int x, y, z, t;
     cb_coords(i, par, ns, x, y, z, t);
     long s = lex_index(x, y, z, t, ns);
-    float2 v = full[s * 12 + k];
+    float2 v = full[net_at(s, k, 2 * Vh)];
     half[tid] = make_double2(v.x, v.y);
 }
 
 // per-block partial sums over the sites of one field (parity mask: -1 all, 0 even, 1 odd)
 //   part_x2[r][b] = sum |x|^2,  with out != null also
 //   part_l[r][b]  = sum |out - x|^2 and g = mask (out - x) * inv_x2[r]
-__global__ void k_pt_loss(const float2 *__restrict__ out, const double2 *__restrict__ x, const double *__restrict__ inv_x2,
+constexpr int kPtLossBS = 1024;  // (few blocks: 40 for 20 fields of 8^3 x 16, 62 us a pass with 256 lanes, 34 us so)
+
+__global__ __launch_bounds__(kPtLossBS) void k_pt_loss(const float2 *__restrict__ out, const double2 *__restrict__ x, const double *__restrict__ inv_x2,
                           float2 *__restrict__ g, double *__restrict__ part, int ns, long V, int par, long chunk)
 {
     const int r = blockIdx.y;
@@ -341,23 +438,26 @@ __global__ void k_pt_loss(const float2 *__restrict__ out, const double2 *__restr
         bool on = par < 0 || ((xx + y + z + t) & 1) == par;
         const double2 *xs = x + ((size_t)r * V + s) * 12;
         if (out) {
-            const float2 *os = out + ((size_t)r * V + s) * 12;
-            float2 *gs = g + ((size_t)r * V + s) * 12;
+            Cx<float> o[12], gs[12];
+            ld12(out + (size_t)r * V * 12, s, V, o);
             double sc = inv_x2[r];
+#pragma unroll
             for (int k = 0; k < 12; k++) {
-                double dr = on ? (double)os[k].x - xs[k].x : 0.0;
-                double di = on ? (double)os[k].y - xs[k].y : 0.0;
+                double dr = on ? (double)o[k].re - xs[k].x : 0.0;
+                double di = on ? (double)o[k].im - xs[k].y : 0.0;
                 acc += dr * dr + di * di;
-                gs[k] = make_float2((float)(dr * sc), (float)(di * sc));
+                gs[k] = Cx<float>{(float)(dr * sc), (float)(di * sc)};
             }
+            st12(g + (size_t)r * V * 12, s, V, gs);
         } else if (on) {
+#pragma unroll
             for (int k = 0; k < 12; k++) acc += xs[k].x * xs[k].x + xs[k].y * xs[k].y;
         }
     }
-    __shared__ double red[kPtBS];
+    __shared__ double red[kPtLossBS];
     red[threadIdx.x] = acc;
     __syncthreads();
-    for (int w = kPtBS / 2; w > 0; w >>= 1) {
+    for (int w = kPtLossBS / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
@@ -433,8 +533,7 @@ void ptnet_prepare(laph_ctx *c, laph_ptnet *net, const double *U)
     // the same address, so the pointer does not identify the field
     long V = c->g.V;
     float2 *lk = (float2 *)ctx_named(c, "net.links", sizeof(float2) * V * 36);
-    hipLaunchKernelGGL(k_pt_from64, dim3(nblocks_for(V * 36, 256)), dim3(256), 0, c->stream, (const double2 *)U, lk,
-                       V * 36);
+    hipLaunchKernelGGL(k_pt_links, dim3(nblocks_for(V, kPtTile)), dim3(kPtBS), 0, c->stream, (const double2 *)U, lk, V);
     LAPH_HIP(hipGetLastError());
     net->links = lk;
     net->wbf_h.resize(net->nw);
@@ -504,18 +603,6 @@ void net_to_eo(laph_ctx *c, const float2 *full, int par, double2 *half)
     LAPH_HIP(hipGetLastError());
 }
 
-// gamma_4 eta for R canonical FP64 fields -> net layout (one channel); gamma_4 swaps the
-// upper and lower spin pairs (chiral basis)
-__global__ void k_g4_to_net(const double2 *__restrict__ eta, float2 *__restrict__ out, long n)
-{
-    long tid = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (tid >= n) return;
-    long s = tid / 12;
-    int k = (int)(tid - s * 12);
-    double2 v = eta[s * 12 + ((k / 3) ^ 2) * 3 + k % 3];
-    out[tid] = make_float2((float)v.x, (float)v.y);
-}
-
 // half[(k*Vh + i)*R + r] = full[r][site(i, par)][k]
 __global__ void k_net_to_eo_batch(const float2 *__restrict__ full, double2 *__restrict__ half, int par, int ns,
                                   long V, long Vh, int R)
@@ -528,7 +615,7 @@ __global__ void k_net_to_eo_batch(const float2 *__restrict__ full, double2 *__re
     int r = (int)(rem - i * R);
     int x, y, z, t;
     cb_coords(i, par, ns, x, y, z, t);
-    float2 v = full[((long)r * V + lex_index(x, y, z, t, ns)) * 12 + k];
+    float2 v = full[(size_t)r * V * 12 + net_at(lex_index(x, y, z, t, ns), k, V)];
     half[tid] = make_double2(v.x, v.y);
 }
 
@@ -537,7 +624,8 @@ void ptnet_initial_guess(laph_ctx *c, laph_ptnet *net, float bct, const double *
     long V = c->g.V, n = V * 12 * R;
     float2 *a = (float2 *)ctx_named(c, "net.x0in", sizeof(float2) * n);
     float2 *b = (float2 *)ctx_named(c, "net.x0out", sizeof(float2) * n);
-    hipLaunchKernelGGL(k_g4_to_net, dim3(nblocks_for(n, 256)), dim3(256), 0, c->stream, (const double2 *)eta, a, n);
+    hipLaunchKernelGGL(k_pt_from64<true>, dim3(nblocks_for(V, kPtTile), R), dim3(kPtBS), 0, c->stream,
+                       (const double2 *)eta, a, V);
     LAPH_HIP(hipGetLastError());
     ptnet_forward(c, net, bct, a, b, R, 0);
     long m = 12 * c->g.Vh * R;
@@ -570,6 +658,20 @@ size_t ptnet_scratch_bytes(const Geom &g, const laph_ptnet *net, int nrhs, int w
     s += ws_align(sizeof(double) * pb * nrhs) + ws_align(sizeof(double) * nrhs);  // loss partials, 1/|x|^2
     s += 3 * ws_align(sizeof(float2) * nw) + ws_align(4 * nw);                     // w32, m1, m2, new BF16
     return s;
+}
+
+// n interface fields <-> planes
+static void from64(laph_ctx *c, const double *in, float2 *out, int n)
+{
+    hipLaunchKernelGGL(k_pt_from64<false>, dim3(nblocks_for(c->g.V, kPtTile), n), dim3(kPtBS), 0, c->stream,
+                       (const double2 *)in, out, c->g.V);
+    LAPH_HIP(hipGetLastError());
+}
+static void to64(laph_ctx *c, const float2 *in, double *out, int n)
+{
+    hipLaunchKernelGGL(k_pt_to64, dim3(nblocks_for(c->g.V, kPtTile), n), dim3(kPtBS), 0, c->stream, in,
+                       (double2 *)out, c->g.V);
+    LAPH_HIP(hipGetLastError());
 }
 
 // ---------------------------------------------------------------------- C-ABI
@@ -673,12 +775,9 @@ extern "C" int laph_ptnet_forward(laph_ctx_t c, laph_ptnet_t net, const double *
     float2 *a = (float2 *)ctx_named(c, "net.in", sizeof(float2) * n);
     float2 *b = (float2 *)ctx_named(c, "net.out", sizeof(float2) * n);
     ptnet_prepare(c, net, U);
-    hipLaunchKernelGGL(k_pt_from64, dim3(nblocks_for(n, 256)), dim3(256), 0, c->stream, (const double2 *)in, a, n);
-    LAPH_HIP(hipGetLastError());
+    from64(c, in, a, n_fields);
     ptnet_forward(c, net, (float)bc_t, a, b, n_fields, 0);
-    hipLaunchKernelGGL(k_pt_to64, dim3(nblocks_for(n, 256)), dim3(256), 0, c->stream, (const float2 *)b,
-                       (double2 *)out, n);
-    LAPH_HIP(hipGetLastError());
+    to64(c, b, out, n_fields);
     LAPH_HIP(hipStreamSynchronize(c->stream));
     LAPH_API_END(c)
 }
@@ -696,15 +795,12 @@ extern "C" int laph_ptnet_backward(laph_ctx_t c, laph_ptnet_t net, const double 
     float2 *g = (float2 *)ctx_named(c, "net.g", sizeof(float2) * n);
     float2 *gi = gin ? (float2 *)ctx_named(c, "net.gin", sizeof(float2) * n) : nullptr;
     ptnet_prepare(c, net, U);
-    hipLaunchKernelGGL(k_pt_from64, dim3(nblocks_for(n, 256)), dim3(256), 0, c->stream, (const double2 *)in, a, n);
-    hipLaunchKernelGGL(k_pt_from64, dim3(nblocks_for(n, 256)), dim3(256), 0, c->stream, (const double2 *)gout, g, n);
-    LAPH_HIP(hipGetLastError());
+    from64(c, in, a, n_fields);
+    from64(c, gout, g, n_fields);
     ptnet_forward(c, net, (float)bc_t, a, b, n_fields, 1);
     ptnet_backward(c, net, (float)bc_t, g, gi, n_fields);
     if (gin) {
-        hipLaunchKernelGGL(k_pt_to64, dim3(nblocks_for(n, 256)), dim3(256), 0, c->stream, (const float2 *)gi,
-                           (double2 *)gin, n);
-        LAPH_HIP(hipGetLastError());
+        to64(c, gi, gin, n_fields);
     }
     std::vector<float> h(2 * net->nw);
     LAPH_HIP(hipMemcpyAsync(h.data(), net->grad, sizeof(float2) * net->nw, hipMemcpyDeviceToHost, c->stream));
@@ -729,8 +825,7 @@ extern "C" int laph_ptnet_train_step(laph_ctx_t c, laph_ptnet_t net, const doubl
     float2 *o = (float2 *)ctx_named(c, "net.out", sizeof(float2) * n);
     float2 *g = (float2 *)ctx_named(c, "net.g", sizeof(float2) * n);
     ptnet_prepare(c, net, U);
-    hipLaunchKernelGGL(k_pt_from64, dim3(nblocks_for(n, 256)), dim3(256), 0, c->stream, (const double2 *)b, a, n);
-    LAPH_HIP(hipGetLastError());
+    from64(c, b, a, n_pairs);
     ptnet_forward(c, net, (float)bc_t, a, o, n_pairs, 1);
     // relative loss sum_r |N(b_r) - x_r|^2 / |x_r|^2 over the selected parity
     long chunk = 16 * kPtBS;
@@ -738,7 +833,7 @@ extern "C" int laph_ptnet_train_step(laph_ctx_t c, laph_ptnet_t net, const doubl
     double *part = (double *)ctx_named(c, "net.part", sizeof(double) * nblk * n_pairs);
     double *inv = (double *)ctx_named(c, "net.inv", sizeof(double) * n_pairs);
     std::vector<double> hp((size_t)nblk * n_pairs), hinv(n_pairs);
-    hipLaunchKernelGGL(k_pt_loss, dim3(nblk, n_pairs), dim3(kPtBS), 0, c->stream, (const float2 *)nullptr,
+    hipLaunchKernelGGL(k_pt_loss, dim3(nblk, n_pairs), dim3(kPtLossBS), 0, c->stream, (const float2 *)nullptr,
                        (const double2 *)x, (const double *)nullptr, (float2 *)nullptr, part, c->g.ns, V,
                        opt->loss_parity, chunk);
     LAPH_HIP(hipGetLastError());
@@ -751,7 +846,7 @@ extern "C" int laph_ptnet_train_step(laph_ctx_t c, laph_ptnet_t net, const doubl
         hinv[r] = 1.0 / s;
     }
     LAPH_HIP(hipMemcpyAsync(inv, hinv.data(), sizeof(double) * n_pairs, hipMemcpyHostToDevice, c->stream));
-    hipLaunchKernelGGL(k_pt_loss, dim3(nblk, n_pairs), dim3(kPtBS), 0, c->stream, (const float2 *)o,
+    hipLaunchKernelGGL(k_pt_loss, dim3(nblk, n_pairs), dim3(kPtLossBS), 0, c->stream, (const float2 *)o,
                        (const double2 *)x, (const double *)inv, g, part, c->g.ns, V, opt->loss_parity, chunk);
     LAPH_HIP(hipGetLastError());
     ptnet_backward(c, net, (float)bc_t, g, nullptr, n_pairs);
