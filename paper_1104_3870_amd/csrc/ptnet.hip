@@ -48,7 +48,7 @@ __device__ __forceinline__ void lex_coords(unsigned s, unsigned ns, int &x, int 
 // the links 36 planes of V float2 [mu][row][column].  (Site records of 96 and 72 bytes made
 // every load of a wave touch 48 to 64 cache lines.  8^3 x 16, 20 fields: a layer of two channels
 // 65 -> 59 us, now bound by its FP32 operations, 768 a lane for each channel and direction; a
-// training step 1.07 -> 0.85 ms with the wave sums and the loss below.)
+// training step 1.07 -> 0.77 ms with the wave sums and the loss below.)
 __device__ __forceinline__ size_t net_at(long s, int k, long V) { return ((size_t)(k >> 1) * V + s) * 2 + (k & 1); }
 
 // Transport matrix of direction d at site (x,y,z,t): the neighbour whose field is
@@ -423,9 +423,8 @@ __global__ void k_net_to_eo(const float2 *__restrict__ full, int par, double2 *_
 // per-block partial sums over the sites of one field (parity mask: -1 all, 0 even, 1 odd)
 //   part_x2[r][b] = sum |x|^2,  with out != null also
 //   part_l[r][b]  = sum |out - x|^2 and g = mask (out - x) * inv_x2[r]
-constexpr int kPtLossBS = 1024;  // (few blocks: 40 for 20 fields of 8^3 x 16, 62 us a pass with 256 lanes, 34 us so)
-
-__global__ __launch_bounds__(kPtLossBS) void k_pt_loss(const float2 *__restrict__ out, const double2 *__restrict__ x, const double *__restrict__ inv_x2,
+// (20 fields of 8^3 x 16: 62 us a pass in 40 blocks, 10.5 us in 640)
+__global__ __launch_bounds__(kPtBS) void k_pt_loss(const float2 *__restrict__ out, const double2 *__restrict__ x, const double *__restrict__ inv_x2,
                           float2 *__restrict__ g, double *__restrict__ part, int ns, long V, int par, long chunk)
 {
     const int r = blockIdx.y;
@@ -454,14 +453,25 @@ __global__ __launch_bounds__(kPtLossBS) void k_pt_loss(const float2 *__restrict_
             for (int k = 0; k < 12; k++) acc += xs[k].x * xs[k].x + xs[k].y * xs[k].y;
         }
     }
-    __shared__ double red[kPtLossBS];
+    __shared__ double red[kPtBS];
     red[threadIdx.x] = acc;
     __syncthreads();
-    for (int w = kPtLossBS / 2; w > 0; w >>= 1) {
+    for (int w = kPtBS / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
     if (threadIdx.x == 0) part[(size_t)r * gridDim.x + blockIdx.x] = red[0];
+}
+
+// total of field r's nb partials; with inv its reciprocal too
+__global__ __launch_bounds__(64) void k_pt_loss_sum(const double *__restrict__ part, int nb, double *total, double *inv)
+{
+    const int r = blockIdx.x, lane = threadIdx.x;
+    double s = lane < nb ? part[(size_t)r * nb + lane] : 0.0;
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane) return;
+    total[r] = s;
+    if (inv) inv[r] = 1.0 / s;
 }
 
 template <int CO>
@@ -486,16 +496,22 @@ void launch_layer(laph_ctx *c, const float2 *links, const float2 *in, float2 *ou
     }
 }
 
+// blocks of a weight gradient over n (field, site) items: a few thousand items per block keep
+// the block reduction cheap; at most 256 blocks
+int wgrad_blocks(long n, long &chunk)
+{
+    chunk = std::max<long>(kPtBS * 8, (n + 255) / 256);
+    chunk = (chunk + kPtBS - 1) / kPtBS * kPtBS;
+    return (int)((n + chunk - 1) / chunk);
+}
+
 template <int CO>
 void launch_wgrad_t(laph_ctx *c, laph_ptnet *net, const float2 *act, const float2 *g, int cin, int nrhs, float bct,
                     float2 *grad)
 {
     long V = c->g.V;
-    long n = V * nrhs;
-    // a few thousand items per block keep the block reduction cheap; at most 256 blocks
-    long chunk = std::max<long>(kPtBS * 8, (n + 255) / 256);
-    chunk = (chunk + kPtBS - 1) / kPtBS * kPtBS;
-    int nblk = (int)((n + chunk - 1) / chunk);
+    long chunk;
+    const int nblk = wgrad_blocks(V * nrhs, chunk);
     long nwl = (long)CO * cin * 144;
     float2 *gpart = (float2 *)ctx_named(c, "net.gpart", sizeof(float2) * nwl * nblk);
     hipLaunchKernelGGL(k_pt_wgrad<CO>, dim3(nblk, cin * 9), dim3(kPtBS), 0, c->stream, net->links,
@@ -646,10 +662,8 @@ size_t ptnet_scratch_bytes(const Geom &g, const laph_ptnet *net, int nrhs, int w
     if (what == 0) return s;
     for (int l = 1; l < net->layers; l++) s += ws_align(fb * net->ch[l]);          // kept activations
     s += ws_align(sizeof(float2) * nw) + ws_align(4 * (size_t)net->cmax * net->cmax * 144);  // grad, wadj
-    const long n = (long)V * nrhs;
-    long chunk = std::max<long>(kPtBS * 8, (n + 255) / 256);
-    chunk = (chunk + kPtBS - 1) / kPtBS * kPtBS;
-    const size_t nblk = (n + chunk - 1) / chunk;
+    long chunk;
+    const size_t nblk = wgrad_blocks((long)V * nrhs, chunk);
     for (int l = 0; l < net->layers; l++)  // the per-layer partial gradients (grow-only name)
         s += ws_align(sizeof(float2) * net->ch[l] * net->ch[l + 1] * 144 * nblk);
     s += ws_align(fb);  // g
@@ -827,28 +841,26 @@ extern "C" int laph_ptnet_train_step(laph_ctx_t c, laph_ptnet_t net, const doubl
     ptnet_prepare(c, net, U);
     from64(c, b, a, n_pairs);
     ptnet_forward(c, net, (float)bc_t, a, o, n_pairs, 1);
-    // relative loss sum_r |N(b_r) - x_r|^2 / |x_r|^2 over the selected parity
-    long chunk = 16 * kPtBS;
-    int nblk = (int)((V + chunk - 1) / chunk);
-    double *part = (double *)ctx_named(c, "net.part", sizeof(double) * nblk * n_pairs);
+    // relative loss sum_r |N(b_r) - x_r|^2 / |x_r|^2 over the selected parity; the partial sums
+    // live in the scratch that the last layer's weight gradient takes next
+    const int last = net->layers - 1;
+    long chunk;
+    const size_t gp = std::max(sizeof(double) * n_pairs, sizeof(float2) * net->ch[last] * net->ch[last + 1] * 144 *
+                                                             wgrad_blocks(V * n_pairs, chunk));
+    double *part = (double *)ctx_named(c, "net.gpart", gp);
+    const int nb = (int)std::min<long>({64, (V + kPtBS - 1) / kPtBS, (long)(gp / (sizeof(double) * n_pairs))});
+    chunk = (V + nb - 1) / nb;
+    double *tot = (double *)ctx_named(c, "net.part", sizeof(double) * n_pairs);
     double *inv = (double *)ctx_named(c, "net.inv", sizeof(double) * n_pairs);
-    std::vector<double> hp((size_t)nblk * n_pairs), hinv(n_pairs);
-    hipLaunchKernelGGL(k_pt_loss, dim3(nblk, n_pairs), dim3(kPtLossBS), 0, c->stream, (const float2 *)nullptr,
-                       (const double2 *)x, (const double *)nullptr, (float2 *)nullptr, part, c->g.ns, V,
-                       opt->loss_parity, chunk);
-    LAPH_HIP(hipGetLastError());
-    LAPH_HIP(hipMemcpyAsync(hp.data(), part, sizeof(double) * hp.size(), hipMemcpyDeviceToHost, c->stream));
-    LAPH_HIP(hipStreamSynchronize(c->stream));
-    for (int r = 0; r < n_pairs; r++) {
-        double s = 0;
-        for (int k = 0; k < nblk; k++) s += hp[(size_t)r * nblk + k];
-        LAPH_CHECK(s > 0, LAPH_EINVAL, "target %d is zero on the selected sites", r);
-        hinv[r] = 1.0 / s;
-    }
-    LAPH_HIP(hipMemcpyAsync(inv, hinv.data(), sizeof(double) * n_pairs, hipMemcpyHostToDevice, c->stream));
-    hipLaunchKernelGGL(k_pt_loss, dim3(nblk, n_pairs), dim3(kPtLossBS), 0, c->stream, (const float2 *)o,
-                       (const double2 *)x, (const double *)inv, g, part, c->g.ns, V, opt->loss_parity, chunk);
-    LAPH_HIP(hipGetLastError());
+    auto pass = [&](const float2 *out, const double *scale, double *reciprocal) {
+        hipLaunchKernelGGL(k_pt_loss, dim3(nb, n_pairs), dim3(kPtBS), 0, c->stream, out, (const double2 *)x, scale, g,
+                           part, c->g.ns, V, opt->loss_parity, chunk);
+        hipLaunchKernelGGL(k_pt_loss_sum, dim3(n_pairs), dim3(64), 0, c->stream, (const double *)part, nb, tot,
+                           reciprocal);
+        LAPH_HIP(hipGetLastError());
+    };
+    pass(nullptr, nullptr, inv);
+    pass(o, inv, nullptr);
     ptnet_backward(c, net, (float)bc_t, g, nullptr, n_pairs);
     // the optimiser state goes to the device for the step and comes back
     const size_t wb = sizeof(float2) * net->nw;
@@ -869,19 +881,19 @@ extern "C" int laph_ptnet_train_step(laph_ctx_t c, laph_ptnet_t net, const doubl
     LAPH_HIP(hipMemcpyAsync(nw32.data(), w32, wb, hipMemcpyDeviceToHost, c->stream));
     LAPH_HIP(hipMemcpyAsync(nm1.data(), m1, wb, hipMemcpyDeviceToHost, c->stream));
     LAPH_HIP(hipMemcpyAsync(nm2.data(), m2, wb, hipMemcpyDeviceToHost, c->stream));
-    LAPH_HIP(hipMemcpyAsync(hp.data(), part, sizeof(double) * hp.size(), hipMemcpyDeviceToHost, c->stream));
+    std::vector<double> ht(n_pairs), hinv(n_pairs);
+    LAPH_HIP(hipMemcpyAsync(ht.data(), tot, sizeof(double) * n_pairs, hipMemcpyDeviceToHost, c->stream));
+    LAPH_HIP(hipMemcpyAsync(hinv.data(), inv, sizeof(double) * n_pairs, hipMemcpyDeviceToHost, c->stream));
     LAPH_HIP(hipStreamSynchronize(c->stream));
+    for (int r = 0; r < n_pairs; r++)
+        LAPH_CHECK(std::isfinite(hinv[r]), LAPH_EINVAL, "target %d is zero on the selected sites", r);
     net->w32.swap(nw32);
     net->m1.swap(nm1);
     net->m2.swap(nm2);
     net->step = step;
     if (loss) {
         double s = 0;
-        for (int r = 0; r < n_pairs; r++) {
-            double q = 0;
-            for (int k = 0; k < nblk; k++) q += hp[(size_t)r * nblk + k];
-            s += q * hinv[r];
-        }
+        for (int r = 0; r < n_pairs; r++) s += ht[r] * hinv[r];
         *loss = s / n_pairs;
     }
     LAPH_API_END(c)
