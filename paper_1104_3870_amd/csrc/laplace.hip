@@ -8,6 +8,29 @@ namespace {
 
 constexpr int kLapLanes = 256;
 
+// the three sums of a block of W waves to sums[b][3]
+template <int W>
+__device__ __forceinline__ void lap_sums(double dre, double dim, double nrm, unsigned b, double *__restrict__ sums)
+{
+    __shared__ double red[3][W];
+    for (int w = 32; w > 0; w >>= 1) {
+        dre += __shfl_down(dre, w, 64);
+        dim += __shfl_down(dim, w, 64);
+        nrm += __shfl_down(nrm, w, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = dre;
+        red[1][threadIdx.x >> 6] = dim;
+        red[2][threadIdx.x >> 6] = nrm;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double v = 0.0;
+        for (int w = 0; w < W; w++) v += red[threadIdx.x][w];
+        sums[(long)b * 3 + threadIdx.x] = v;
+    }
+}
+
 // one lane per (slice t, spatial site), a workgroup's sites in one slice; vectors of slice t
 // start at base + t * stride.  DOT: block sums of <dot, out> and |out|^2 (see lap_fused)
 template <bool DOT>
@@ -78,30 +101,77 @@ __global__ __launch_bounds__(kLapLanes) void k_lap(const double2 *__restrict__ u
         }
     }
     }
-    if (DOT) {
-        __shared__ double red[3][kLapLanes / 64];
-        for (int w = 32; w > 0; w >>= 1) {
-            dre += __shfl_down(dre, w, 64);
-            dim += __shfl_down(dim, w, 64);
-            nrm += __shfl_down(nrm, w, 64);
+    if (DOT) lap_sums<kLapLanes / 64>(dre, dim, nrm, b, sums);
+}
+
+// The same with one lane per (slice, site, colour row), three waves for a workgroup's 64 sites
+// of one slice: on small lattices the kernel above leaves most of the chip idle while each of
+// its few waves waits for 72 loads
+template <bool DOT>
+__global__ __launch_bounds__(192) void k_lap_rows(const double2 *__restrict__ us, const double2 *__restrict__ in,
+                                             long in_stride, const double2 *__restrict__ prev, long prev_stride,
+                                             double2 *__restrict__ out, long out_stride, int ns, int nt, long V,
+                                             double alpha, double beta, double gamma, int nblk,
+                                             const double2 *__restrict__ dot, long dot_stride, double *__restrict__ sums)
+{
+    const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+    const int t = (int)(b / nblk);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), row = wave;
+    const unsigned V3 = (unsigned)(V / nt), r = (b - (unsigned)t * nblk) * 64 + (threadIdx.x & 63);
+    double dre = 0.0, dim = 0.0, nrm = 0.0;
+    if (r < V3) {
+    const unsigned q1 = r / (unsigned)ns, q2 = q1 / (unsigned)ns;
+    const int x = (int)(r - q1 * ns), y = (int)(q1 - q2 * ns), z = (int)q2;
+    const double2 *vin = in + t * in_stride;
+    const double2 self = vin[r * 3 + row];
+    double2 acc = cscale(self, -6.0);
+    us += (long)t * V3;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        int xp = x, yp = y, zp = z, xm = x, ym = y, zm = z;
+        if (k == 0) {
+            xp = x + 1 == ns ? 0 : x + 1;
+            xm = x == 0 ? ns - 1 : x - 1;
+        } else if (k == 1) {
+            yp = y + 1 == ns ? 0 : y + 1;
+            ym = y == 0 ? ns - 1 : y - 1;
+        } else {
+            zp = z + 1 == ns ? 0 : z + 1;
+            zm = z == 0 ? ns - 1 : z - 1;
         }
-        if ((threadIdx.x & 63) == 0) {
-            red[0][threadIdx.x >> 6] = dre;
-            red[1][threadIdx.x >> 6] = dim;
-            red[2][threadIdx.x >> 6] = nrm;
-        }
-        __syncthreads();
-        if (threadIdx.x < 3) {
-            double v = 0.0;
-            for (int w = 0; w < kLapLanes / 64; w++) v += red[threadIdx.x][w];
-            sums[(long)b * 3 + threadIdx.x] = v;
+        const unsigned rp = xp + ns * (yp + ns * zp), rm = xm + ns * (ym + ns * zm);
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            acc = cadd(acc, cmul(us[(long)(k * 9 + row * 3 + c) * V + r], vin[rp * 3 + c]));
+            acc = cadd(acc, cconjmul(us[(long)(k * 9 + c * 3 + row) * V + rm], vin[rm * 3 + c]));
         }
     }
+    double2 o = cadd(cscale(acc, alpha), cscale(self, beta));
+    if (prev) o = cadd(o, cscale(prev[t * prev_stride + r * 3 + row], gamma));
+    out[t * out_stride + r * 3 + row] = o;
+    if (DOT) {
+        const double2 q = dot[t * dot_stride + r * 3 + row];
+        dre = q.x * o.x + q.y * o.y;
+        dim = q.x * o.y - q.y * o.x;
+        nrm = cnorm2(o);
+    }
+    }
+    if (DOT) lap_sums<3>(dre, dim, nrm, b, sums);
 }
 
 }  // namespace
 
-int lap_blocks(const Geom &g) { return (int)((g.V3 + kLapLanes - 1) / kLapLanes); }
+// sites up to which three lanes a site are faster (a step, one lane / three): 4^3 x 8 5.1 / 3.2 us,
+// 8^3 x 16 5.5 / 3.3, 12^3 x 24 6.1 / 5.3, 16^3 x 32 14.9 / 15.2 (5.0 TB/s), 24^3 x 128 249 / 315;
+// eigenvectors of 10^3 x 16 13.8 / 12.2 ms, 12^3 x 24 21.0 / 20.6, 14^3 x 20 28.0 / 29.1
+constexpr long kLapRowsMost = 32768;
+static bool lap_rows(const Geom &g) { return g.V <= kLapRowsMost; }
+
+int lap_blocks(const Geom &g)
+{
+    const int sites = lap_rows(g) ? 64 : kLapLanes;
+    return (int)((g.V3 + sites - 1) / sites);
+}
 
 void lap_fused(laph_ctx *c, const double2 *us, const double2 *in, long in_stride, const double2 *prev,
                long prev_stride, double2 *out, long out_stride, double alpha, double beta, double gamma,
@@ -109,12 +179,14 @@ void lap_fused(laph_ctx *c, const double2 *us, const double2 *in, long in_stride
 {
     const int nblk = lap_blocks(c->g);
     const dim3 grid((unsigned)(nblk * (long)c->g.nt));
-    if (sums)
-        hipLaunchKernelGGL(k_lap<true>, grid, dim3(kLapLanes), 0, c->stream, us, in, in_stride, prev, prev_stride, out,
+    auto launch = [&](auto kernel, int lanes) {
+        hipLaunchKernelGGL(kernel, grid, dim3(lanes), 0, c->stream, us, in, in_stride, prev, prev_stride, out,
                            out_stride, c->g.ns, c->g.nt, c->g.V, alpha, beta, gamma, nblk, dot, dot_stride, sums);
+    };
+    if (lap_rows(c->g))
+        sums ? launch(k_lap_rows<true>, 192) : launch(k_lap_rows<false>, 192);
     else
-        hipLaunchKernelGGL(k_lap<false>, grid, dim3(kLapLanes), 0, c->stream, us, in, in_stride, prev, prev_stride, out,
-                           out_stride, c->g.ns, c->g.nt, c->g.V, alpha, beta, gamma, nblk, dot, dot_stride, sums);
+        sums ? launch(k_lap<true>, kLapLanes) : launch(k_lap<false>, kLapLanes);
     LAPH_HIP(hipGetLastError());
 }
 
