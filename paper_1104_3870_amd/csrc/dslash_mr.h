@@ -16,6 +16,7 @@ struct MrArgs {
     int ns, nt;
     long Vh;
     int R;
+    int S;           // sites per block (set by the launcher; S R lanes compute, all of the block stage)
     int par;
     double a, c;
     double wt, ws, bct;

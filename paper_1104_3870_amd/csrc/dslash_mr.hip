@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256) LAPH_LDS_ATTR void k_dslash_lds(const MrArgs P
 {
     extern __shared__ float4 smem[];
     const int R = P.R;
-    const int S = blockDim.x / R;  // sites per block
+    const int S = P.S;
     float4 *slk = smem;                 // [S][8][kLkF4]
     float4 *scl = smem + S * 8 * kLkF4;  // [S][18]
     const long Vh = P.Vh;
@@ -855,7 +855,10 @@ void launch_dslash_mr(laph_ctx *c, int mode, const MrArgs &a, hipStream_t st)
     b.m_A = b.wby ? umulhi_magic(A) : 0;
     b.unit = 1.0f;
     b.tgauge = a.tgauge;
-    dim3 grid(nblocks_for(a.Vh, S)), block(S * a.R);
+    b.S = S;
+    // lanes enough to stage the block's 8 S links in two turns: with one right-hand side 64
+    // lanes took eight, and 18 for the clover blocks (4^3 x 8, FP16: 18.9 us a hop, 11.5 us with 256)
+    dim3 grid(nblocks_for(a.Vh, S)), block(std::max(S * a.R, std::min(256, (8 * S + 63) / 64 * 64)));
     hipEvent_t e0, e1;
     timing_begin(c, &e0, &e1);
     const bool hx = a.x != nullptr;
