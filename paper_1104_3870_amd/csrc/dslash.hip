@@ -285,10 +285,10 @@ __device__ __forceinline__ void wave_sum_rhs(double (&q)[3], int R)
 
 // kStage (R = 8, 16 or 32 right-hand sides: a block holds 256 / R whole sites): the block's
 // links and clover elements go through LDS.  Read per lane they are half of the bytes the
-// vector cache returns although all R lanes of a site read the same ones, and that return
-// path, 90% busy, bound the kernel.  24^3 x 32, R = 32: 1.50 -> 1.16 ms (1.13 with the
-// walk's tiles below, 4.8 TB/s of the traffic behind L2); 16^3 x 32: 458 -> 363 us;
-// R = 16: 799 -> 610, R = 8 on 16^3 x 32: 135 -> 119 us.
+// vector cache returns, although all R lanes of a site read the same ones, and they push the
+// neighbours' records out of it.  24^3 x 32, R = 32: 1.50 -> 1.16 ms, 1.13 with the walk's
+// tiles below, now bound by the traffic behind L2 (9.8 -> 8.2 GB, 7.2 TB/s); 16^3 x 32:
+// 458 -> 363 us; R = 16: 799 -> 610, R = 8 on 16^3 x 32: 135 -> 119 us.
 template <class SP, class GP, class CP, int MODE, bool O32, bool kStage>
 __global__ __launch_bounds__(256) void k_dslash(const DslashArgs P)
 {
