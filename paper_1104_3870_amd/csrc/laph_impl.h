@@ -192,6 +192,7 @@ struct laph_ctx {
     void *pin = nullptr;
     unsigned pin_seq = 0;
     hipEvent_t pin_ev = nullptr;
+    unsigned long long *pin_fp = nullptr;  // pinned block sums of the field's fingerprint
     // timing
     struct TimeAcc {
         double ms = 0, bytes = 0;
