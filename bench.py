@@ -287,7 +287,7 @@ def main():
     ap.add_argument("--workload", default="ns24_nt128")
     ap.add_argument("--precision", default="f16")
     ap.add_argument("--block", type=int, default=0, help="right-hand sides per batch (0: the autotuner's choice)")
-    ap.add_argument("--graph", type=int, default=1, help="the solver's use_graph hint")
+    ap.add_argument("--graph", type=int, default=1, help="replay the Krylov iteration from HIP graphs")
     ap.add_argument("--solver", default="bicgstab", choices=["cgnr", "bicgstab"],
                     help="Krylov method of the headline and plain FP64 forms: the paper's even-odd "
                          "BiCGStab, or CG on the normal equations (its fallback)")
@@ -437,7 +437,7 @@ def main():
     for k in range(args.warmup):
         st = step(k, best)
         log("warmup %d: iters %s" % (k, sorted(s.iters for s in st)[::8]))
-    # the production form: no per-kernel events
+    # the production form: no per-kernel events (they would also switch the graphs off)
     iters, resid = [], []
     torch.cuda.synchronize()
     t0 = time.time()
@@ -451,7 +451,7 @@ def main():
     value = nsrc * args.steps / elapsed
 
     # ---------------- instrumented step: the same kernels and launch shapes with HIP events
-    # around every hopping launch on the library's stream, for the roofline
+    # around every hopping launch on the library's stream (graphs off), for the roofline
     P.laph_set_timing(L.ctx, True)
     P.laph_get_timing(L.ctx, reset=True)
     torch.cuda.synchronize()
@@ -671,7 +671,8 @@ def main():
     dom = tm[0] if tm else {"kernel": "none", "ms": 0.0, "launches": 0, "bytes": 0.0}
     roofline = hop_roofline(dom)
     roofline["measured"] = ("HIP events around every hopping launch on the library's stream during one "
-                            "instrumented step after the timed region (same kernels and launch shapes)")
+                            "instrumented step after the timed region (same kernels and launch shapes; "
+                            "graphs off in that step)")
     roofline["share_of_instrumented_step"] = round(dom["ms"] / (1000 * t_ins), 3) if t_ins > 0 else None
     # the same against the measured streaming rate of the box (a plain device copy)
     cp, cp_how = copy_peak_gbs()
@@ -723,9 +724,10 @@ def main():
                    "lattice": [cfg.ns, cfg.ns, cfg.ns, cfg.nt], "nv": cfg.nv, "m0": cfg.m0,
                    "dilution": cfg.dilution, "sources_per_step": nsrc,
                    "form": "even-odd %s, %s inner vectors, %d right-hand sides per batch (%s), FP64 reliable "
-                           "updates%s" % (
+                           "updates, iteration %s%s" % (
                                args.solver.upper(), args.precision, block,
                                "autotuned" if args.block == 0 else "fixed",
+                               "replayed from HIP graphs" if args.graph else "launched eagerly",
                                ", initial guess from the trained PT-net" if guess_net else "")},
         "mean_iters": float(np.mean(iters)),
         "max_true_resid": float(max(resid)),

@@ -254,8 +254,9 @@ typedef struct {
     int reliable_every; /* most iterations between FP64 reliable updates (mixed precision) */
     int block_rhs;      /* right-hand sides iterated together (power of two <= 32); 0 = the
                            block size laph_autotune picks (run on first use) */
-    int use_graph;      /* a hint that the iteration may be replayed from HIP graphs; no solver
-                           does, plain launches are the faster ones.  Results are the same */
+    int use_graph;      /* replay the Krylov iteration's hops and reductions from HIP graphs
+                           (mixed-precision BiCGStab, CGNR; not with timing on): fewer launches
+                           for the host, the same results */
     const void *net;    /* learned network (laph_ptnet_t) or NULL: the right preconditioner of
                            LAPH_SOLVER_FGMRES; with the other solvers the initial guess
                            x0 = N(gamma_4 eta) on odd sites (N approximates K^-1) */

@@ -193,6 +193,7 @@ extern "C" int laph_destroy(laph_ctx_t c)
     (void)hipStreamSynchronize(c->stream);
     cache_release_all(c);
     scratch_reset(c);
+    if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->pin) (void)hipHostFree(c->pin);
     if (c->pin_fp) (void)hipHostFree(c->pin_fp);
     if (c->pin_ev) (void)hipEventDestroy(c->pin_ev);

@@ -187,6 +187,7 @@ struct laph_ctx {
     // tiled walk, tile_override > 0 fixes the sites per block
     int walk_mode = 0;
     int tile_override = 0;
+    hipStream_t cap_stream = nullptr;  // capture stream for HIP graphs (default priority)
     // pinned host memory of the solver's scalars (slots written or read by kernels), the number
     // of the last iteration that got a slot, and the event after the last read of a written slot
     void *pin = nullptr;

@@ -1507,6 +1507,7 @@ struct Work {
     int R;
     Scal *sc;      // device
     double *part;  // device partials [kMaxBlocks][R][4]
+    bool use_graph = false;  // replay the iteration's launches from HIP graphs
     double delta2 = 0.01;    // reliable update when |res|^2 fell below delta2 times its last FP64 value
     int dirs = 0;            // direction buffers of the fused CG loop (0: the default)
     bool x_zero = false;     // x_hi is known to be zero (the first residual is bhat itself)
@@ -1663,6 +1664,68 @@ struct UpdateVote {
     bool want() const { return deep || all_conv() || quorum(); }
 };
 
+// The launches of an iteration replayed from HIP graphs (use_graph; not with timing on, whose
+// events are per launch): one graph per position of the iteration's buffer ring, recorded on
+// the context's capture stream the first time the position comes up and launched on the
+// solve's stream from then on.  What a graph holds must not change from one turn of the ring
+// to the next, so the last finalisation, which carries the iteration's number to the host,
+// stays outside.  A replay keeps the host to three launches an iteration; the GPU pays some
+// 5 us before each and a solve the recording (eager / replayed: four sources on 4^3 x 8, FP16
+// BiCGStab, 2.88 / 3.12 ms; 20 on 8^3 x 16, FP32 CG, 5.73 / 6.18; 32 on 16^3 x 32, FP16 BiCGStab,
+// 168.1 / 169.3, CG 115.0 / 116.0).
+struct IterGraphs {
+    laph_ctx *c;
+    bool on;
+    hipGraphExec_t exec[kMaxDirs] = {};
+    int replays = 0;  // reported under LAPH_VERBOSE
+    IterGraphs(laph_ctx *ctx, bool use) : c(ctx), on(use && !ctx->timing) {}
+    ~IterGraphs()
+    {
+        bool any = false;
+        for (hipGraphExec_t e : exec) any = any || e;
+        if (any) (void)hipStreamSynchronize(c->stream);  // (the last replay may still run)
+        for (hipGraphExec_t e : exec)
+            if (e) (void)hipGraphExecDestroy(e);
+    }
+    // body(stream) puts the launches of ring position pos on the context's stream, which it
+    // gets as an argument too
+    template <class F>
+    void run(int pos, F body)
+    {
+        if (!on) {
+            body(c->stream);
+            return;
+        }
+        if (!exec[pos]) record(pos, body);
+        LAPH_HIP(hipGraphLaunch(exec[pos], c->stream));
+        replays++;
+    }
+    template <class F>
+    void record(int pos, F body)
+    {
+        if (!c->cap_stream) LAPH_HIP(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
+        hipStream_t main = c->stream;
+        hipGraph_t g = nullptr;
+        LAPH_HIP(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed));
+        c->stream = c->cap_stream;
+        try {
+            body(c->cap_stream);
+        } catch (...) {  // the capture is ended and the solve's stream put back in any case
+            (void)hipStreamEndCapture(c->cap_stream, &g);
+            if (g) (void)hipGraphDestroy(g);
+            c->stream = main;
+            throw;
+        }
+        c->stream = main;
+        LAPH_HIP(hipStreamEndCapture(c->cap_stream, &g));
+        const hipError_t e = hipGraphInstantiate(&exec[pos], g, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(g);
+        LAPH_HIP(e);
+    }
+    IterGraphs(const IterGraphs &) = delete;
+    IterGraphs &operator=(const IterGraphs &) = delete;
+};
+
 // rhi = bhat - Mhat xhi for masked RHS (FP64), then r2hi / masks (rlo: the residual in
 // storage precision SP instead of rhi, for the right-hand sides it is formed for)
 template <class SP = S64>
@@ -1689,10 +1752,7 @@ void true_eo_residual(Work &w, const Op64 &hi, Vec bhat, Vec xhi, Vec tmp, Vec r
 // p = r + beta (p - omega v).  The steps alpha p + omega s are owed to the FP32 increment
 // in a ring of K (p, s) pairs and taken K at a time; FP64 reliable updates (quorum rule of
 // the CG loop) fold them with the increment into x_hi and replace r by the FP64 residual.
-// Decisions read the previous iteration's scalars, as in the CG loop.  The launches go to
-// the stream one by one: replayed from a HIP graph per ring position they had no gaps inside
-// an iteration but 4-8 us at either end of it, and 8 graphs to build per solve (a solve of 20
-// sources on 8^3 x 16 6.47 ms, with graphs 7.08 ms; 16^3 x 32 160.7 / 161.0 ms).
+// Decisions read the previous iteration's scalars, as in the CG loop.
 template <class SP, class GP, class CP, class XP>
 void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, Vec rhi, Vec tmp64,
                     int maxiter, int reliable_every, std::vector<Scal> &hs)
@@ -1738,13 +1798,20 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         return d;
     };
     Turn turn{}, prev{};  // this iteration's and the previous one's (seq 0: none)
+    IterGraphs graphs(c, w.use_graph);
+    Op<SP, GP, CP> op = lo;
     auto body = [&](int b) {
-        lo.mhat_dot(pb[b], v, r0, part_hop);
-        launch_fin_rows(c, k_fin_bs_alpha<false>, k_fin_bs_alpha<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre, w.sc);
-        launch_el(c, k_s_update<SP>, n, r, v, sb[b], w.Vh, w.R, (const Scal *)w.sc);
-        lo.mhat_dot(sb[b], t, sb[b], part_hop);
-        launch_fin_rows(c, k_fin_bs_omega<false>, k_fin_bs_omega<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre, w.sc);
-        launch_el(c, k_bs_r<SP>, n, sb[b], t, r, r0, w.Vh, w.R, part_hop, (const Scal *)w.sc);
+        graphs.run(b, [&](hipStream_t st) {
+            op.st = st;
+            op.mhat_dot(pb[b], v, r0, part_hop);
+            launch_fin_rows(c, k_fin_bs_alpha<false>, k_fin_bs_alpha<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre,
+                            w.sc);
+            launch_el(c, k_s_update<SP>, n, r, v, sb[b], w.Vh, w.R, (const Scal *)w.sc);
+            op.mhat_dot(sb[b], t, sb[b], part_hop);
+            launch_fin_rows(c, k_fin_bs_omega<false>, k_fin_bs_omega<true>, w.R, 3 * w.R, part_hop, nblk_hop, part_pre,
+                            w.sc);
+            launch_el(c, k_bs_r<SP>, n, sb[b], t, r, r0, w.Vh, w.R, part_hop, (const Scal *)w.sc);
+        });
         launch_fin_rows(c, k_fin_bs_beta<false>, k_fin_bs_beta<true>, w.R, 3 * w.R, part_hop, nblk_el, part_pre, w.sc,
                         turn.pin, turn.seq);
     };
@@ -1811,8 +1878,8 @@ void bicgstab_fused(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat,
         }
     }
     if (laph_verbose())
-        fprintf(stderr, "[laph] bicgstab reliable updates: all converged %d, deep drop %d, quorum %d, count %d\n", why[0],
-                why[1], why[2], why[3]);
+        fprintf(stderr, "[laph] bicgstab reliable updates: all converged %d, deep drop %d, quorum %d, count %d; "
+                "graph replays %d\n", why[0], why[1], why[2], why[3], graphs.replays);
     // steps still owed after the last iteration, then the increment of every RHS (inactive
     // ones hold what they had when they stopped)
     if (nowed) launch_el(c, k_fold_x_bs<XP, SP>, n, xhi, xlo, owed(1, nowed), w.Vh, w.R, (const Scal *)w.sc);
@@ -1977,7 +2044,8 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
     // the fused body leaves the steps x += alpha p to the direction update; with K direction
     // buffers (a ring) each update writes the new direction into the next buffer and keeps
     // the old ones, and every K-th update takes the K owed steps at once: the FP32 increment
-    // is read and written every K-th iteration only
+    // is read and written every K-th iteration only (graph replay keeps one recorded body per
+    // direction buffer)
     const int K = !fuse ? 1 : w.dirs > 0 ? w.dirs : kDefaultDirs;
     Vec pb[kMaxDirs];
     pb[0] = p;
@@ -2000,25 +2068,33 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
     const bool lag = !plain;
     int nupd = 0;  // reliable updates (reported under LAPH_VERBOSE)
     Turn turn{}, prev{};  // this iteration's and the previous one's (seq 0: none)
+    IterGraphs graphs(c, w.use_graph);
+    Op<SP, GP, CP> op = lo;
     auto body = [&]() {
-        if constexpr (!plain) {
-            // M p with |q|^2 and A^-1 gamma_5 q from its epilogue; M^dag q feeding the CG
-            // update directly (partials of the fused epilogues are block-major)
-            lo.mhat_prep(p, q, to, part_hop);
-            launch_fin_rows(c, k_fin_cg_alpha<kFromPre>, k_fin_cg_alpha<kFromHop>, w.R, w.R, part_hop, nblk_hop,
-                            part_pre, w.sc);
-            lo.mhat_dag_cg(q, to, r, (const Scal *)w.sc, part_hop);
+        graphs.run(cur, [&](hipStream_t st) {
+            op.st = st;
+            if constexpr (!plain) {
+                // M p with |q|^2 and A^-1 gamma_5 q from its epilogue; M^dag q feeding the CG
+                // update directly (partials of the fused epilogues are block-major)
+                op.mhat_prep(p, q, to, part_hop);
+                launch_fin_rows(c, k_fin_cg_alpha<kFromPre>, k_fin_cg_alpha<kFromHop>, w.R, w.R, part_hop, nblk_hop,
+                                part_pre, w.sc);
+                op.mhat_dag_cg(q, to, r, (const Scal *)w.sc, part_hop);
+            } else {
+                op.mhat(p, q);
+                launch_red(c, k_normsq<SP>, n, q, w.Vh, w.R, w.part);
+                launch_fin(c, k_fin_cg_alpha<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc);
+                op.mhat_dag(q, y, to);
+                launch_red(c, k_cg_update<SP, XP, true>, n, xlo, p, res, q, r, y, w.Vh, w.R, w.part,
+                           (const Scal *)w.sc);
+                launch_fin(c, k_fin_cg_beta<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc, 1, 0,
+                           (PinSlot *)nullptr, 0u);
+                launch_el(c, k_cg_p<SP, XP>, n, p, owed_dirs(0, 1), r, xlo, w.Vh, w.R, (const Scal *)w.sc, 0, 0);
+            }
+        });
+        if constexpr (!plain)
             launch_fin_rows(c, k_fin_cg_beta<kFromPre>, k_fin_cg_beta<kFromHop>, w.R, w.R, part_hop, nblk_hop,
                             part_pre, w.sc, 0, 1, turn.pin, turn.seq);
-        } else {
-            lo.mhat(p, q);
-            launch_red(c, k_normsq<SP>, n, q, w.Vh, w.R, w.part);
-            launch_fin(c, k_fin_cg_alpha<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc);
-            lo.mhat_dag(q, y, to);
-            launch_red(c, k_cg_update<SP, XP, true>, n, xlo, p, res, q, r, y, w.Vh, w.R, w.part, (const Scal *)w.sc);
-            launch_fin(c, k_fin_cg_beta<kFromBlocks>, w.R, (const double *)w.part, nblk, w.R, w.sc, 1, 0, (PinSlot *)nullptr, 0u);
-            launch_el(c, k_cg_p<SP, XP>, n, p, owed_dirs(0, 1), r, xlo, w.Vh, w.R, (const Scal *)w.sc, 0, 0);
-        }
     };
     for (int it = 0; it < maxiter;) {
         int chunk = std::min(check_every, maxiter - it);
@@ -2093,7 +2169,8 @@ void cgnr(Work &w, const Op<SP, GP, CP> &lo, const Op64 &hi, Vec bhat, Vec xhi, 
             nowed = take ? 0 : nowed + 1;
         }
     }
-    if (laph_verbose() && !plain) fprintf(stderr, "[laph] cgnr reliable updates: %d\n", nupd);
+    if (laph_verbose())
+        fprintf(stderr, "[laph] cgnr reliable updates: %d; graph replays %d\n", nupd, graphs.replays);
     // steps still owed after the last iteration (the latest takes the current alpha)
     if (nowed)
         launch_el(c, k_fold_x_step<XP, SP>, n, xhi, xlo, owed_dirs(1, nowed), w.Vh, w.R, (const Scal *)w.sc);
@@ -2516,6 +2593,7 @@ void solve_batch(laph_ctx *c, const double *eta, double *x, int R, int nreal, co
     long Vh = c->g.Vh;
     DiracCache &dc = *c->cur;
     Work w{c, Vh, R, nullptr, nullptr};
+    w.use_graph = sv->use_graph != 0;
     if (sv->reliable_delta > 0) w.delta2 = sv->reliable_delta * sv->reliable_delta;
     w.dirs = sv->dir_buffers;
     w.sc = (Scal *)ctx_named(c, "slv.scal", sizeof(Scal) * R);
