@@ -600,20 +600,23 @@ double dslash_bytes(long Vh, int R, int gbytes, int cbytes, int sbytes, bool has
     return (double)Vh * (site + R * per_rhs);
 }
 
+[[noreturn]] static void bad_mode(int mode) { laph_fail(LAPH_EINVAL, "no FP64 hopping kernel with epilogue mode %d", mode); }
+
 template <class SP, class GP, class CP, bool kStage>
 void launch_modes(int mode, dim3 grid, dim3 block, size_t lds, hipStream_t st, const DslashArgs &a)
 {
     switch (mode) {
-    case M_PLAIN: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_PLAIN, true, kStage>), grid, block, lds, st, a); break;
-    case M_INV_AFTER: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER, true, kStage>), grid, block, lds, st, a); break;
-    case M_INV_OF_SUM: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_OF_SUM, true, kStage>), grid, block, lds, st, a); break;
+    case M_PLAIN: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_PLAIN, true, kStage>), grid, block, lds, st, a); return;
+    case M_INV_AFTER: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER, true, kStage>), grid, block, lds, st, a); return;
+    case M_INV_OF_SUM: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_OF_SUM, true, kStage>), grid, block, lds, st, a); return;
+    case M_CLOV_ADD: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_CLOV_ADD, true, kStage>), grid, block, lds, st, a); return;
     case M_INV_AFTER_DOT:
         if constexpr (!kStage) {
             hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_INV_AFTER_DOT, true, false>), grid, block, lds, st, a);
-            break;
+            return;
         }
-    default: hipLaunchKernelGGL((k_dslash<SP, GP, CP, M_CLOV_ADD, true, kStage>), grid, block, lds, st, a); break;
     }
+    bad_mode(mode);
 }
 
 // pairs up to which the split kernel is the faster one (between events, rolled against split):
@@ -625,12 +628,13 @@ void launch_split(int mode, long n, hipStream_t st, const DslashArgs &a)
 {
     const dim3 grid(nblocks_for(n, kSplit)), block(12 * kSplit);
     switch (mode) {
-    case M_PLAIN: hipLaunchKernelGGL(k_dslash_split<M_PLAIN>, grid, block, 0, st, a); break;
-    case M_INV_AFTER: hipLaunchKernelGGL(k_dslash_split<M_INV_AFTER>, grid, block, 0, st, a); break;
-    case M_INV_OF_SUM: hipLaunchKernelGGL(k_dslash_split<M_INV_OF_SUM>, grid, block, 0, st, a); break;
-    case M_INV_AFTER_DOT: hipLaunchKernelGGL(k_dslash_split<M_INV_AFTER_DOT>, grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL(k_dslash_split<M_CLOV_ADD>, grid, block, 0, st, a); break;
+    case M_PLAIN: hipLaunchKernelGGL(k_dslash_split<M_PLAIN>, grid, block, 0, st, a); return;
+    case M_INV_AFTER: hipLaunchKernelGGL(k_dslash_split<M_INV_AFTER>, grid, block, 0, st, a); return;
+    case M_INV_OF_SUM: hipLaunchKernelGGL(k_dslash_split<M_INV_OF_SUM>, grid, block, 0, st, a); return;
+    case M_CLOV_ADD: hipLaunchKernelGGL(k_dslash_split<M_CLOV_ADD>, grid, block, 0, st, a); return;
+    case M_INV_AFTER_DOT: hipLaunchKernelGGL(k_dslash_split<M_INV_AFTER_DOT>, grid, block, 0, st, a); return;
     }
+    bad_mode(mode);
 }
 
 int dslash_dot_parts(long Vh, int R)
