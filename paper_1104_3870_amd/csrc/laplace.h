@@ -3,7 +3,7 @@
 
 #include "laph_impl.h"
 
-// workgroups of one slice
+// workgroups of one slice in a launch with sums
 int lap_blocks(const Geom &g);
 // out = alpha Lap(in) + beta in + gamma prev on every slice; vectors of slice t start at
 // ptr + t * stride (complex elements).  sums (may be null) takes, per slice and workgroup, Re

@@ -31,9 +31,10 @@ __device__ __forceinline__ void lap_sums(double dre, double dim, double nrm, uns
     }
 }
 
-// one lane per (slice t, spatial site), a workgroup's sites in one slice; vectors of slice t
-// start at base + t * stride.  DOT: block sums of <dot, out> and |out|^2 (see lap_fused)
-template <bool DOT>
+// one lane per (slice t, spatial site), a workgroup's sites in one slice, or (FLAT) in several;
+// vectors of slice t start at base + t * stride.  DOT: block sums of <dot, out> and |out|^2 (see
+// lap_fused)
+template <bool DOT, bool FLAT>
 __global__ __launch_bounds__(kLapLanes) void k_lap(const double2 *__restrict__ us, const double2 *__restrict__ in,
                                              long in_stride, const double2 *__restrict__ prev, long prev_stride,
                                              double2 *__restrict__ out, long out_stride, int ns, int nt, long V,
@@ -41,10 +42,14 @@ __global__ __launch_bounds__(kLapLanes) void k_lap(const double2 *__restrict__ u
                                              const double2 *__restrict__ dot, long dot_stride, double *__restrict__ sums)
 {
     const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int t = (int)(b / nblk);
-    const long V3 = V / nt, r = (long)(b - (unsigned)t * nblk) * kLapLanes + threadIdx.x, s = (long)t * V3 + r;
+    const long V3 = V / nt;
+    // (32-bit division: 27 links of 16 bytes a site keep V far below 2^32)
+    const unsigned flat = b * kLapLanes + threadIdx.x;
+    const int t = (int)(FLAT ? flat / (unsigned)V3 : b / nblk);
+    const long r = FLAT ? (long)flat - (long)t * V3 : (long)(b - (unsigned)t * nblk) * kLapLanes + threadIdx.x;
+    const long s = (long)t * V3 + r;
     double dre = 0.0, dim = 0.0, nrm = 0.0;
-    if (r < V3) {
+    if (FLAT ? s < V : r < V3) {
     int x = (int)(r % ns);
     long q = r / ns;
     int y = (int)(q % ns);
@@ -165,28 +170,37 @@ __global__ __launch_bounds__(192) void k_lap_rows(const double2 *__restrict__ us
 // 8^3 x 16 5.5 / 3.3, 12^3 x 24 6.1 / 5.3, 16^3 x 32 14.9 / 15.2 (5.0 TB/s), 24^3 x 128 249 / 315;
 // eigenvectors of 10^3 x 16 13.8 / 12.2 ms, 12^3 x 24 21.0 / 20.6, 14^3 x 20 28.0 / 29.1
 constexpr long kLapRowsMost = 32768;
-static bool lap_rows(const Geom &g) { return g.V <= kLapRowsMost; }
-
-int lap_blocks(const Geom &g)
+// slices that leave half of a one-lane workgroup idle or more (2^3, 4^3): several of them share one
+// (a step of 2^3 x 8192 6.5 us, a slice each 89; 4^3 x 1024 6.5, 12.8; but 6^3 x 256 6.3, 6.0, 10^3 x
+// 48 6.5, 5.9), and where sums per slice are asked for, the workgroups of 64 sites take them (29 us
+// and 6.6)
+static bool lap_small_slice(const Geom &g) { return 2 * g.V3 <= kLapLanes; }
+static bool lap_rows(const Geom &g, bool sums) { return g.V <= kLapRowsMost || (sums && lap_small_slice(g)); }
+static int lap_slice_blocks(const Geom &g, bool rows)
 {
-    const int sites = lap_rows(g) ? 64 : kLapLanes;
+    const int sites = rows ? 64 : kLapLanes;
     return (int)((g.V3 + sites - 1) / sites);
 }
+
+int lap_blocks(const Geom &g) { return lap_slice_blocks(g, lap_rows(g, true)); }
 
 void lap_fused(laph_ctx *c, const double2 *us, const double2 *in, long in_stride, const double2 *prev,
                long prev_stride, double2 *out, long out_stride, double alpha, double beta, double gamma,
                const double2 *dot, long dot_stride, double *sums)
 {
-    const int nblk = lap_blocks(c->g);
-    const dim3 grid((unsigned)(nblk * (long)c->g.nt));
+    const bool rows = lap_rows(c->g, sums), flat = !rows && lap_small_slice(c->g);
+    const int nblk = lap_slice_blocks(c->g, rows);
+    const dim3 grid(flat ? nblocks_for(c->g.V, kLapLanes) : (unsigned)(nblk * (long)c->g.nt));
     auto launch = [&](auto kernel, int lanes) {
         hipLaunchKernelGGL(kernel, grid, dim3(lanes), 0, c->stream, us, in, in_stride, prev, prev_stride, out,
                            out_stride, c->g.ns, c->g.nt, c->g.V, alpha, beta, gamma, nblk, dot, dot_stride, sums);
     };
-    if (lap_rows(c->g))
+    if (rows)
         sums ? launch(k_lap_rows<true>, 192) : launch(k_lap_rows<false>, 192);
+    else if (flat)
+        launch(k_lap<false, true>, kLapLanes);
     else
-        sums ? launch(k_lap<true>, kLapLanes) : launch(k_lap<false>, kLapLanes);
+        sums ? launch(k_lap<true, false>, kLapLanes) : launch(k_lap<false, false>, kLapLanes);
     LAPH_HIP(hipGetLastError());
 }
 
