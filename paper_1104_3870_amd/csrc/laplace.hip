@@ -166,20 +166,24 @@ __global__ __launch_bounds__(192) void k_lap_rows(const double2 *__restrict__ us
 
 }  // namespace
 
-// sites up to which three lanes a site are faster (a step, one lane / three): 4^3 x 8 5.1 / 3.2 us,
-// 8^3 x 16 5.5 / 3.3, 12^3 x 24 6.1 / 5.3, 16^3 x 32 14.9 / 15.2 (5.0 TB/s), 24^3 x 128 249 / 315;
-// eigenvectors of 10^3 x 16 13.8 / 12.2 ms, 12^3 x 24 21.0 / 20.6, 14^3 x 20 28.0 / 29.1
-constexpr long kLapRowsMost = 32768;
+// workgroups of 64 sites up to which three lanes a site are faster: three for each of the 256 CUs,
+// which hold them all at once (a step, one lane / three: 4^3 x 8 5.1 / 3.2 us, 8^3 x 16 5.5 / 3.3;
+// 648 workgroups, 12^3 x 24, 5.7 / 5.4; 756, 12^3 x 28, 6.2 / 5.8; 768, 16^3 x 12, 6.1 / 5.7 and
+// 8^3 x 96 5.8 / 5.5; 774, 14^3 x 18, 6.4 / 6.9; 896, 16^3 x 14, 6.4 / 7.1; 24^3 x 128 249 / 315)
+constexpr long kLapRowsMost = 768;
 // slices that leave half of a one-lane workgroup idle or more (2^3, 4^3): several of them share one
 // (a step of 2^3 x 8192 6.5 us, a slice each 89; 4^3 x 1024 6.5, 12.8; but 6^3 x 256 6.3, 6.0, 10^3 x
 // 48 6.5, 5.9), and where sums per slice are asked for, the workgroups of 64 sites take them (29 us
 // and 6.6)
 static bool lap_small_slice(const Geom &g) { return 2 * g.V3 <= kLapLanes; }
-static bool lap_rows(const Geom &g, bool sums) { return g.V <= kLapRowsMost || (sums && lap_small_slice(g)); }
 static int lap_slice_blocks(const Geom &g, bool rows)
 {
     const int sites = rows ? 64 : kLapLanes;
     return (int)((g.V3 + sites - 1) / sites);
+}
+static bool lap_rows(const Geom &g, bool sums)
+{
+    return (long)lap_slice_blocks(g, true) * g.nt <= kLapRowsMost || (sums && lap_small_slice(g));
 }
 
 int lap_blocks(const Geom &g) { return lap_slice_blocks(g, lap_rows(g, true)); }

@@ -1,5 +1,6 @@
 """Laplacian and Chebyshev step on many small slices, where a workgroup's sites come from several
-of them and the last one is ragged, against the oracle.
+of them and the last one is ragged, and on either side of the 768 workgroups up to which three
+lanes work on a site, against the oracle.
 
 Bound: a component is a sum of 19 products of unit-size links with field values; 64 roundings of
 the largest value a step can reach (12 times the field's) covers it."""
@@ -13,7 +14,8 @@ from gpu_util import dev, host, say
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("ns,nt", [(2, 8202), (4, 770), (6, 202), (10, 50)])
+@pytest.mark.parametrize("ns,nt", [(2, 8202), (4, 770), (6, 202), (10, 50), (2, 768),
+                                   (2, 770), (12, 28), (16, 12), (14, 18)])
 def test_many_slices(ns, nt):
     import torch
 

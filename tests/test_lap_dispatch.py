@@ -67,7 +67,7 @@ int main(int argc, char **argv)
 """
 
 LATTICES = [(2, 2), (2, 8), (4, 8), (8, 16), (12, 24), (14, 16), (14, 20), (16, 10), (16, 12), (16, 32), (24, 16), (24, 128),
-            (2, 8192), (4, 640), (4, 1024), (6, 160), (6, 256), (10, 60)]
+            (12, 28), (14, 18), (16, 14), (2, 2048), (2, 8192), (4, 640), (4, 1024), (6, 160), (6, 256), (10, 60)]
 
 
 @pytest.fixture(scope="module")
@@ -110,3 +110,10 @@ def test_sums_per_slice(launches):
         blocks, grid, lanes, kernel = launches[ns, nt, 1]
         assert grid == blocks * nt and "<true" in kernel
         assert blocks * lanes >= (3 if "k_lap_rows" in kernel else 1) * ns ** 3
+
+
+def test_lanes_per_site(launches):
+    """Three lanes a site up to 768 workgroups of 64 sites, where they were measured the faster."""
+    for ns, nt in LATTICES:
+        _, _, _, kernel = launches[ns, nt, 0]
+        assert ("k_lap_rows" in kernel) == (-(-ns ** 3 // 64) * nt <= 768), (ns, nt, kernel)
