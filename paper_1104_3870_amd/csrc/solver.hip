@@ -159,7 +159,7 @@ __device__ __forceinline__ void send_scal(const Scal *sc, int r, int n, PinSlot 
     __threadfence_system();
     __syncthreads();
     if ((int)threadIdx.x < n)
-        __hip_atomic_store(&pin->seq[r + threadIdx.x], seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&pin->seq[r + threadIdx.x], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ------------------------------------------------------------------ BiCGStab kernels
@@ -1561,7 +1561,8 @@ enum { kPinIter, kPinRead = 2, kPinWrite, kPinSums, kPinSlots };
 static PinSlot *pinned_slot(laph_ctx *c, int slot)
 {
     if (!c->pin) {
-        LAPH_HIP(hipHostMalloc(&c->pin, sizeof(PinSlot) * kPinSlots, hipHostMallocDefault));
+        // (coherent by name: the host reads a slot while later kernels of the stream still run)
+        LAPH_HIP(hipHostMalloc(&c->pin, sizeof(PinSlot) * kPinSlots, hipHostMallocCoherent | hipHostMallocMapped));
         memset(c->pin, 0, sizeof(PinSlot) * kPinSlots);
     }
     if (!c->pin_ev) LAPH_HIP(hipEventCreateWithFlags(&c->pin_ev, hipEventDisableTiming));
