@@ -170,4 +170,5 @@ void launch_clover_apply(laph_ctx *c, const void *clov, const void *x, const flo
 // partial sums per right-hand side and value that an M_INV_AFTER_DOT launch writes
 int dslash_dot_parts(long Vh, int R);
 
-double dslash_bytes(long Vh, int R, int gbytes, int cbytes, int sbytes, bool has_norm, int mode, bool has_x);
+double dslash_bytes(long Vh, int R, int gbytes, int cbytes, int sbytes, bool has_norm, int mode, bool has_x,
+                    bool y_is_x);

@@ -590,13 +590,16 @@ __global__ __launch_bounds__(256) void k_clover_apply(const typename CP::E *__re
 
 }  // namespace
 
-double dslash_bytes(long Vh, int R, int gbytes, int cbytes, int sbytes, bool has_norm, int mode, bool has_x)
+double dslash_bytes(long Vh, int R, int gbytes, int cbytes, int sbytes, bool has_norm, int mode, bool has_x,
+                    bool y_is_x)
 {
     // algorithmic bytes: 8 links, the clover block set if used, one input spinor per
-    // site (neighbour re-reads are cache traffic), the output and the epilogue operand
+    // site (neighbour re-reads are cache traffic), the output, the epilogue operand and the
+    // dot epilogue's y where it is another field
     double site = 8.0 * 9 * gbytes;
     if (mode != M_PLAIN) site += 72.0 * cbytes;
-    double per_rhs = 12.0 * sbytes * (2 + (has_x ? 1 : 0)) + (has_norm ? 4.0 * (2 + (has_x ? 1 : 0)) : 0.0);
+    const int streams = 2 + (has_x ? 1 : 0) + (mode == M_INV_AFTER_DOT && !y_is_x ? 1 : 0);
+    double per_rhs = 12.0 * sbytes * streams + (has_norm ? 4.0 * streams : 0.0);
     return (double)Vh * (site + R * per_rhs);
 }
 
@@ -672,9 +675,10 @@ void launch_dslash(laph_ctx *c, int mode, const DslashArgs &a, hipStream_t st)
     else
         launch_modes<SP, GP, CP, false>(mode, grid, block, 0, st, b);
     LAPH_HIP(hipGetLastError());
-    bool has_x = a.x != nullptr && (mode != M_PLAIN || a.x);
     if (e0)
-        timing_end(c, e0, e1, dslash_bytes(a.Vh, a.R, GP::bytes, CP::bytes, SP::bytes, SP::kNorm, mode, has_x),
+        timing_end(c, e0, e1,
+                   dslash_bytes(a.Vh, a.R, GP::bytes, CP::bytes, SP::bytes, SP::kNorm, mode, a.x != nullptr,
+                                a.dot_y == a.x),
                    timing_label("dslash", SP::bytes == 16 ? "f64" : "f32", mode, a.R));
 }
 

@@ -2,7 +2,8 @@
 device side, the HIP runtime's launch calls replaced by a recorder.  Every epilogue mode has to
 reach its own instantiation on every route (few pairs: the split kernel; 8, 16 or 32 right-hand
 sides: staged, except the dot epilogue; else the rolled one), and a mode without one has to fail
-instead of running another epilogue."""
+instead of running another epilogue.  The bytes a launch reports to the timing are those of its
+links, its clover term and every field it reads or writes."""
 import os
 import shutil
 import subprocess
@@ -46,8 +47,9 @@ const char *hipGetErrorString(hipError_t) { return ""; }
 }
 thread_local laph_ctx *g_current_ctx;
 void laph_fail(int code, const char *, ...) { throw LaphError{code}; }
-void timing_begin(laph_ctx *, hipEvent_t *a, hipEvent_t *b) { *a = *b = nullptr; }
-void timing_end(laph_ctx *, hipEvent_t, hipEvent_t, double, const char *) {}
+static double bytes;
+void timing_begin(laph_ctx *, hipEvent_t *a, hipEvent_t *b) { *a = *b = (hipEvent_t)1; }
+void timing_end(laph_ctx *, hipEvent_t, hipEvent_t, double n, const char *) { bytes = n; }
 const char *timing_label(const char *, const char *, int, int) { return ""; }
 
 template <class F>
@@ -81,6 +83,21 @@ int main()
         });
         show("split", mode, 0, 32, [&] { launch_split(mode, 64, nullptr, DslashArgs{}); });
     }
+    // fields read beside the input: x, and y of the dot epilogue where it is another one
+    const double f[2] = {};
+    for (int mode : {M_PLAIN, M_INV_AFTER, M_INV_AFTER_DOT})
+        for (int x = mode == M_INV_AFTER_DOT; x < 2; x++)
+            for (int y = 0; y < (mode == M_INV_AFTER_DOT ? 2 : 1); y++) {
+                DslashArgs a{};
+                a.ns = 8;
+                a.nt = 4;
+                a.Vh = 1024;
+                a.R = 4;
+                a.x = x ? f : nullptr;
+                a.dot_y = f + y;
+                launch_dslash<S64, G64, C64>(&c, mode, a, nullptr);
+                printf("bytes|%d|%d|%d|%.0f\n", mode, x, y, bytes);
+            }
 }
 """
 
@@ -114,6 +131,12 @@ def test_every_mode_reaches_its_kernel(tmp_path):
     seen = 0
     for line in filter(None, out):
         what, mode, Vh, R, got = line.split("|")
+        if what == "bytes":
+            x, y = int(Vh), int(R)
+            links, clover = 8 * 9 * 16, 0 if int(mode) == PLAIN else 72 * 8
+            assert float(got) == 1024 * (links + clover + 4 * 12 * 16 * (2 + x + y)), line
+            seen += 1
+            continue
         assert _want(what, int(mode), int(Vh) * int(R), int(R)) in got, line
         seen += 1
-    assert seen == 8 * (6 * 7 + 2)
+    assert seen == 8 * (6 * 7 + 2) + 6
