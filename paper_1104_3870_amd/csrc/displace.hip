@@ -129,18 +129,24 @@ __global__ void k_phase(double2 *ph, int ns, int k0, int k1, int k2)
 
 // O[t][n][m] = sum_{x, c} conj(a[t][n][x][c]) ph[x] b[t][m][x][c]: per slice the product
 // A^dag (ph B) over K = 3 Ns^3 on the FP64 matrix cores, the conjugate and the phase applied
-// while staging
+// while staging; with parts > 1 the sum over x in that many pieces, out[t][piece][n][m]
 struct OverlapS {
     const double2 *pa, *pb, *ph;
     double2 *out;
-    int M, N, K;  // na, nb, 3 Ns^3
+    int M, N, K;  // na, nb, 3 Ns^3 / parts
     int tiles_m, tiles_n;
-    long batches;
-    __device__ zg::Side a(long t) const { return {pa + t * M * (long)K, K, 1, M, 1, nullptr}; }
-    __device__ zg::Side b(long t) const { return {pb + t * N * (long)K, K, 1, N, 0, ph}; }
-    __device__ void store(long t, int m, int n, double re, double im) const
+    long batches;  // nt parts
+    int parts;
+    __device__ zg::Side side(const double2 *p, long bt, int rows, int conj, const double2 *phase) const
     {
-        out[(t * M + m) * (long)N + n] = make_double2(re, im);
+        const long t = bt / parts, q = bt - t * parts, full = (long)K * parts;
+        return {p + t * rows * full + q * K, full, 1, rows, conj, phase ? phase + q * (K / 3) : nullptr};
+    }
+    __device__ zg::Side a(long bt) const { return side(pa, bt, M, 1, nullptr); }
+    __device__ zg::Side b(long bt) const { return side(pb, bt, N, 0, ph); }
+    __device__ void store(long bt, int m, int n, double re, double im) const
+    {
+        out[(bt * M + m) * (long)N + n] = make_double2(re, im);
     }
 };
 
@@ -178,14 +184,15 @@ extern "C" int laph_displace(laph_ctx_t c, const double *U, int dir, int sign, i
 }
 
 void overlap_slices(laph_ctx *c, const double2 *a, int na, const double2 *b, int nb, int k0, int k1, int k2,
-                    double2 *phase, double2 *out)
+                    double2 *phase, double2 *out, int parts)
 {
     const long V3 = c->g.V3;
+    LAPH_CHECK(parts >= 1 && V3 % (4L * parts) == 0, LAPH_EINVAL, "%d pieces of a slice", parts);
     hipLaunchKernelGGL(k_phase, dim3(nblocks_for(V3, 256)), dim3(256), 0, c->stream, phase, c->g.ns, k0, k1, k2);
     const int gn = (na + zg::kTM - 1) / zg::kTM, gm = (nb + zg::kTN - 1) / zg::kTN;
     LAPH_CHECK(gm <= 65535 && c->g.nt <= 65535, LAPH_EINVAL, "too many fields for one launch");
     LAPH_CHECK(3 * V3 < (1L << 31), LAPH_EINVAL, "slice too large");
-    OverlapS os{a, b, phase, out, na, nb, (int)(3 * V3), gn, gm, c->g.nt};
+    OverlapS os{a, b, phase, out, na, nb, (int)(3 * V3 / parts), gn, gm, (long)c->g.nt * parts, parts};
     LAPH_CHECK(zg::grid_of(os) < (1L << 31), LAPH_EINVAL, "too many fields for one launch");
     hipLaunchKernelGGL((zg::k_zgemm<12, true, true, OverlapS>), dim3((unsigned)zg::grid_of(os)), dim3(256), 0, c->stream, os);
     LAPH_HIP(hipGetLastError());

@@ -300,14 +300,28 @@ __global__ __launch_bounds__(256) void k_gs_scale(const double2 *__restrict__ w,
     if (row < n) q[t * qslice + row] = cscale(w[t * n + row], 1.0 / nrm[t]);
 }
 
-// dev[t] = max_ap |O[t][a][p] - delta_ap| of the Gram matrices O [nt][nv][nv]
-__global__ __launch_bounds__(256) void k_gram_dev(const double2 *__restrict__ O, int nv, double *__restrict__ dev)
+// pieces the Gram matrices' sums over a slice's sites are taken in, of 64 sites or more: one sum
+// after the other over all 3 Ns^3 terms puts their rounding into the result, which on plane
+// waves, terms all of one size, goes one way (24^3, N_v = 112: 1.2e-12 reported for vectors
+// orthonormal to 4.7e-13)
+int gram_parts(long V3)
+{
+    long d = std::max(1L, V3 / 64);
+    while ((V3 / 4) % d) d--;
+    return (int)d;
+}
+
+// dev[t][block] = max over the block's share of (a, p) of |O[t][a][p] - delta_ap| for the Gram
+// matrices given in pieces, O [nt][parts][nv][nv]
+__global__ __launch_bounds__(256) void k_gram_dev(const double2 *__restrict__ O, int nv, int parts,
+                                                  double *__restrict__ dev)
 {
     __shared__ double red[256];
-    const int t = blockIdx.x;
+    const int t = blockIdx.y;
     double mx = 0.0;
-    for (int e = threadIdx.x; e < nv * nv; e += 256) {
-        double2 v = O[(long)t * nv * nv + e];
+    for (int e = blockIdx.x * 256 + threadIdx.x; e < nv * nv; e += 256 * gridDim.x) {
+        double2 v = make_double2(0.0, 0.0);
+        for (int q = 0; q < parts; q++) v = cadd(v, O[((long)t * parts + q) * nv * nv + e]);
         if (e / nv == e % nv) v.x -= 1.0;
         mx = fmax(mx, sqrt(cnorm2(v)));
     }
@@ -317,7 +331,7 @@ __global__ __launch_bounds__(256) void k_gram_dev(const double2 *__restrict__ O,
         if ((int)threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) dev[t] = red[0];
+    if (threadIdx.x == 0) dev[(long)t * gridDim.x + blockIdx.x] = red[0];
 }
 
 // partial |w|^2 (no update)
@@ -1029,13 +1043,16 @@ extern "C" int laph_eigvecs(laph_ctx_t c, const double *U, const laph_stout *sto
         stats->matvecs = matvecs;
         stats->max_residual = maxres;
         // orthonormality of the output: max |<v_a, v_p> - delta_ap| over slices, from the Gram
-        // matrices (in the buffer of k_rotate, whose m n > nv nv + V3 double2 per slice they fit)
+        // matrices (in the buffer of k_rotate, whose 3 m V3 double2 per slice they fit with the
+        // phase: V3 / 64 pieces of nv nv < 147 m at most)
         double2 *gram = b.Qt + c->g.V3;
-        overlap_slices(c, (const double2 *)evecs, nv, (const double2 *)evecs, nv, 0, 0, 0, b.Qt, gram);
-        hipLaunchKernelGGL(k_gram_dev, dim3(nt), dim3(256), 0, st, (const double2 *)gram, nv, b.lam);
+        const int parts = gram_parts(c->g.V3);
+        const unsigned gb = std::min(rb, 16u);  // (npart holds rb values a slice)
+        overlap_slices(c, (const double2 *)evecs, nv, (const double2 *)evecs, nv, 0, 0, 0, b.Qt, gram, parts);
+        hipLaunchKernelGGL(k_gram_dev, dim3(gb, nt), dim3(256), 0, st, (const double2 *)gram, nv, parts, b.npart);
         LAPH_HIP(hipGetLastError());
-        std::vector<double> dev(nt);
-        LAPH_HIP(hipMemcpyAsync(dev.data(), b.lam, nt * 8, hipMemcpyDeviceToHost, st));
+        std::vector<double> dev((size_t)nt * gb);
+        LAPH_HIP(hipMemcpyAsync(dev.data(), b.npart, dev.size() * 8, hipMemcpyDeviceToHost, st));
         LAPH_HIP(hipStreamSynchronize(st));
         const double mo = *std::max_element(dev.begin(), dev.end());
         stats->max_orth = mo;

@@ -258,9 +258,10 @@ void tgauge_fix(laph_ctx *c, const double *U, double *G, double *Up);
 void tgauge_spinor(laph_ctx *c, const double *G, const double *in, double *out, int nrhs, int dag);
 
 // displace.hip: out[t][i][j] = sum_{x,c} exp(-2 pi i k.x / Ns) conj(a_i) b_j of two sets of colour
-// fields (laph_mom_overlap); phase: scratch of V3 complex numbers
+// fields (laph_mom_overlap); phase: scratch of V3 complex numbers.  parts: the sum over x in that many
+// pieces of whole multiples of four sites, out[t][piece][i][j]
 void overlap_slices(laph_ctx *c, const double2 *a, int na, const double2 *b, int nb, int k0, int k1, int k2,
-                    double2 *phase, double2 *out);
+                    double2 *phase, double2 *out, int parts = 1);
 
 // stout.hip
 void stout_smear_device(laph_ctx *c, const double *U, double rho, int nsteps, double *out);
