@@ -27,8 +27,9 @@
  * (laph_set_workspace, sized by laph_workspace_bytes).  The derived operator is cached for
  * the last gauge field seen, keyed by the field's address and a fingerprint of its
  * contents, so a field changed in place or a new field at a freed one's address is
- * noticed; laph_forget_gauge() drops the cache.  The library keeps one small pinned host
- * buffer per context for the solver's scalar readback.
+ * noticed; laph_forget_gauge() drops the cache.  The library keeps two small pinned host
+ * buffers per context from their first use on: the solver's scalars (67 KB) and the block
+ * sums of the fingerprint (8 KB, every call that takes a Dirac operator).
  * Every call enqueues work on the context's HIP stream; calls that return statistics
  * synchronise that stream.  One context per stream; contexts share nothing.
  *

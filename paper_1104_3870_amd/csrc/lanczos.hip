@@ -758,7 +758,7 @@ __global__ __launch_bounds__(256) void k_phase_out(const double2 *__restrict__ Q
 struct Bufs {
     double2 *Q, *Qt, *w, *w0, *w1, *coef;
     double *T, *M, *Y, *theta, *ylast, *diag, *nb, *nrm, *alpha, *npart, *beta, *lam, *dpart;
-    int *flags, *bflag, *nlock, *nlock_old, *ncols, *ycol, *perm, *src;
+    int *flags, *nsw, *nlock, *nlock_old, *ncols, *ycol, *perm, *src;
 };
 
 }  // namespace
@@ -823,7 +823,7 @@ extern "C" int laph_eigvecs(laph_ctx_t c, const double *U, const laph_stout *sto
     b.lam = (double *)ctx_named(c, "eig.lam", (size_t)nt * 8);
     b.dpart = (double *)ctx_named(c, "eig.dpart", (size_t)nt * rb * 16);
     b.flags = (int *)ctx_named(c, "eig.flags", (size_t)nt * 4);
-    b.bflag = (int *)ctx_named(c, "eig.bflag", (size_t)nt * 4);
+    b.nsw = (int *)ctx_named(c, "eig.nsw", (size_t)nt * 4);
     b.nlock = (int *)ctx_named(c, "eig.nlock", (size_t)nt * 4);
     b.nlock_old = (int *)ctx_named(c, "eig.nlock_old", (size_t)nt * 4);
     b.ncols = (int *)ctx_named(c, "eig.ncols", (size_t)nt * 4);
@@ -843,7 +843,6 @@ extern "C" int laph_eigvecs(laph_ctx_t c, const double *U, const laph_stout *sto
     std::vector<double> Anorm(nt, 0.0);
     LAPH_HIP(hipMemcpyAsync(b.nlock, h_nlock.data(), nt * 4, hipMemcpyHostToDevice, st));
     LAPH_HIP(hipMemsetAsync(b.T, 0, (size_t)nt * m * m * 8, st));
-    LAPH_HIP(hipMemsetAsync(b.bflag, 0, (size_t)nt * 4, st));
 
     dim3 g2(rb, nt);
     // start vector: Philox draws, normalised
@@ -924,9 +923,9 @@ extern "C" int laph_eigvecs(laph_ctx_t c, const double *U, const laph_stout *sto
             const int until = std::min(kJacSweeps, sw + 10);
             for (; sw < until; sw += most) {
                 hipLaunchKernelGGL(k_jacobi_sweeps, dim3(nt), dim3(kJacLanes), jac_lds, st, b.M, b.Qt, rstride, m,
-                                   (const int *)b.nlock, most, b.bflag, b.flags);
+                                   (const int *)b.nlock, most, b.nsw, b.flags);
                 hipLaunchKernelGGL(k_jacobi_vectors, dim3((m + kJacRows - 1) / kJacRows, nt), dim3(256), 0, st, b.Y,
-                                   (const double2 *)b.Qt, rstride, m, (const int *)b.nlock, (const int *)b.bflag,
+                                   (const double2 *)b.Qt, rstride, m, (const int *)b.nlock, (const int *)b.nsw,
                                    sw == 0 ? 1 : 0);
             }
             hipLaunchKernelGGL(k_ritz, dim3(nt), dim3(256), 0, st, (const double *)b.M, (const double *)b.Y,
