@@ -120,12 +120,17 @@ __device__ __forceinline__ void clover_site(const float4 *cl, long i, const Cx<f
 // 8 S links of the block (hop weight, boundary factor and for M_PLAIN the output factor
 // folded in; backward links stored as their adjoint) and its S clover blocks are staged
 // in LDS once, so a lane does only the spin projection, one SU(3) product per direction
-// and the clover product, with explicit FMA chains.  The kernel is bound by VALU issue:
-// neighbour records come through buffer loads (one offset register each) in a software-
-// pipelined direction loop, the record scale and the gamma_5 sign ride on the
-// accumulating FMAs, index divisions are multiply-highs, unit links of a temporal gauge
-// are skipped, the sites are walked in tiles through time (MrArgs::wby) and outputs are
-// stored non-temporally.
+// and the clover product, with explicit FMA chains.  Neighbour records come through buffer
+// loads (one offset register each) in a software-pipelined direction loop, the record scale
+// and the gamma_5 sign ride on the accumulating FMAs, index divisions are multiply-highs,
+// unit links of a temporal gauge are skipped, the sites are walked in tiles through time
+// (MrArgs::wby) and outputs are stored non-temporally.
+// What bounds it is no single unit (FP16, R = 32, 24^3 x 32, `inv` 265 us, 4.7 waves per SIMD):
+// a SIMD issues a VALU instruction every 1.9 ns, where chains of FMAs, products, sums or moves
+// issue one in 1.05-1.1 ns and mixed FMAs, conversions and integer products one in 1.8, so VALU
+// issue takes 0.6 of the time; a wave spends 47% of its time waiting for memory or a barrier,
+// 24% for an issue slot and 0.2% for LDS; the counted traffic runs at 4.5 (`inv_dot` 5.7) of the
+// 6.2 TB/s a streaming kernel reaches.
 constexpr int kLkF4 = 5;  // float4 per staged link (18 floats used)
 
 __device__ __forceinline__ Cx<float> cmul_f(Cx<float> a, Cx<float> b)
